@@ -53,6 +53,7 @@ struct swe_ctx {
     int *d_ev = nullptr, *d_nb = nullptr;
     unsigned char *d_nbk = nullptr;
     signed char *d_p = nullptr;
+    int *d_iperm = nullptr;               // user -> internal element index
     void *d_C[2] = {nullptr, nullptr}, *d_U[2] = {nullptr, nullptr};
     void *d_L = nullptr, *d_src = nullptr;
     int *d_flag = nullptr;
@@ -152,12 +153,12 @@ void free_mesh(swe_ctx *c)
     if (c->d_item_off) (void)hipFree(c->d_item_off);
     c->d_items = nullptr;
     c->d_item_off = nullptr;
-    void *ptrs[] = {c->d_vtx, c->d_ev, c->d_nb, c->d_nbk, c->d_p, c->d_C[0], c->d_C[1],
+    void *ptrs[] = {c->d_vtx, c->d_ev, c->d_nb, c->d_nbk, c->d_p, c->d_iperm, c->d_C[0], c->d_C[1],
                     c->d_U[0], c->d_U[1], c->d_L, c->d_src, c->d_flag, c->d_part, c->d_mass,
                     c->d_inlist, c->d_Lb, c->d_Lc, c->d_list, c->d_cnt, c->d_pnew, c->d_I};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
-    c->d_vtx = nullptr; c->d_ev = nullptr; c->d_nb = nullptr; c->d_nbk = nullptr; c->d_p = nullptr;
+    c->d_vtx = nullptr; c->d_ev = nullptr; c->d_nb = nullptr; c->d_nbk = nullptr; c->d_p = nullptr; c->d_iperm = nullptr;
     c->d_C[0] = c->d_C[1] = c->d_U[0] = c->d_U[1] = nullptr;
     c->d_L = c->d_src = nullptr;
     c->d_flag = nullptr; c->d_part = nullptr; c->d_mass = nullptr;
@@ -703,54 +704,60 @@ swe_status refresh_orders(swe_ctx *c)
     return SWE_OK;
 }
 
-// host [elem][3][K] physical -> device SoA reference-scaled (buffer buf);
-// modes above each element's current order are dropped
+// Caller elements a device staging buffer of `bytes` holds at n values each.
+int64_t stage_elements(size_t bytes, int n) { return std::max<int64_t>(1, (int64_t)(bytes / (sizeof(double) * n))); }
+
+// host [elem][3][K] physical -> device SoA reference-scaled (dst); modes above
+// each element's current order (the device's order map) are dropped.  The
+// right-hand-side scratch takes the caller's values (in two parts where the
+// state is FP32).  On a non-finite value dst may be partly written: callers
+// pass an array whose contents are free until this returns SWE_OK.
 swe_status upload_state(swe_ctx *c, const double *coef, void *dst)
 {
-    if (swe_status st = refresh_orders(c)) return st;
-    const int K = c->K, S = c->stride;
-    const size_t n = (size_t)3 * K * S;
-    std::vector<double> h(n, 0.0);
-    for (int64_t ie = 0; ie < c->ne; ++ie) {
-        const int ue = c->e_perm[ie];
-        const int Ke = K_OF[c->p[ie]];
-        const double inv = 1.0 / c->sfac[ie];
-        for (int j = 0; j < 3; ++j)
-            for (int q = 0; q < K; ++q) {
-                double v = q < Ke ? coef[((size_t)ue * 3 + j) * K + q] : 0.0;
-                if (!std::isfinite(v)) return fail(c, SWE_EINVAL, "non-finite coefficient in state");
-                h[((size_t)j * K + q) * S + ie] = v * inv;
-            }
+    const int K = c->K;
+    const int64_t part = stage_elements(c->rsz * 3 * K * (size_t)c->stride, 3 * K);
+    double *st = static_cast<double *>(c->d_L);
+    HIP_TRY(c, dzero(c, c->d_flag + 1, sizeof(int)));
+    for (int64_t u0 = 0; u0 < c->ne; u0 += part) {
+        const int64_t u1 = std::min(c->ne, u0 + part);
+        HIP_TRY(c, h2d(c, st, coef + (size_t)u0 * 3 * K, sizeof(double) * 3 * K * (size_t)(u1 - u0)));
+        HIP_TRY(c, launch_unpack(c->fp32, st, K, c->d_iperm, view(c), (int)u0, (int)u1, dst, c->d_flag + 1, c->s_base));
     }
-    if (c->fp32) {
-        std::vector<float> f(n);
-        for (size_t i = 0; i < n; ++i) f[i] = (float)h[i];
-        HIP_TRY(c, h2d(c, dst, f.data(), n * sizeof(float)));
-    } else {
-        HIP_TRY(c, h2d(c, dst, h.data(), n * sizeof(double)));
+    int bad = 0;
+    HIP_TRY(c, d2h(c, &bad, c->d_flag + 1, sizeof(int)));
+    return bad ? fail(c, SWE_EINVAL, "non-finite coefficient in state") : SWE_OK;
+}
+
+// device SoA (src, index offset first, stride) -> host [elem][ncomp][K]
+// physical, through the device staging buffer st of `bytes`
+swe_status download(swe_ctx *c, const void *src, int stride, int first, int ncomp, double *out, void *st, size_t bytes)
+{
+    const int n = ncomp * c->K;
+    const int64_t part = stage_elements(bytes, n);
+    for (int64_t u0 = 0; u0 < c->ne; u0 += part) {
+        const int64_t u1 = std::min(c->ne, u0 + part);
+        HIP_TRY(c, launch_pack(c->fp32, src, stride, first, n, c->d_iperm, c->d_vtx, c->d_ev, c->stride, (int)u0, (int)u1,
+                               static_cast<double *>(st), c->s_base));
+        HIP_TRY(c, d2h(c, out + (size_t)u0 * n, st, sizeof(double) * n * (size_t)(u1 - u0)));
     }
     return SWE_OK;
 }
 
-swe_status download(swe_ctx *c, const void *src, int ncomp, double *out, bool is_rhs)
+// one of the context's own arrays, through the right-hand-side scratch
+swe_status download(swe_ctx *c, const void *src, int ncomp, double *out)
 {
-    const int K = c->K, S = c->stride;
-    const size_t n = (size_t)ncomp * K * S;
-    std::vector<double> h(n);
-    if (c->fp32) {
-        std::vector<float> f(n);
-        HIP_TRY(c, d2h(c, f.data(), src, n * sizeof(float)));
-        for (size_t i = 0; i < n; ++i) h[i] = f[i];
-    } else {
-        HIP_TRY(c, d2h(c, h.data(), src, n * sizeof(double)));
-    }
-    (void)is_rhs;
-    for (int64_t ie = 0; ie < c->ne; ++ie) {
-        const int ue = c->e_perm[ie];
-        for (int j = 0; j < ncomp; ++j)
-            for (int q = 0; q < K; ++q)
-                out[((size_t)ue * ncomp + j) * K + q] = h[((size_t)j * K + q) * S + ie] * c->sfac[ie];
-    }
+    return download(c, src, c->stride, 0, ncomp, out, c->d_L, c->rsz * 3 * c->K * (size_t)c->stride);
+}
+
+// the right-hand-side scratch itself (or an array read while it is in use),
+// through state buffer 1, which is left all zero (its contents between calls
+// only have to be zero above each element's order)
+swe_status download_scratch(swe_ctx *c, const void *src, double *out)
+{
+    const size_t bytes = c->rsz * 3 * c->K * (size_t)c->stride;
+    swe_status st = download(c, src, c->stride, 0, 3, out, c->d_C[1], bytes);
+    if (st) return st;
+    HIP_TRY(c, dzero(c, c->d_C[1], bytes));
     return SWE_OK;
 }
 
@@ -913,7 +920,7 @@ swe_status relayout(swe_ctx *c, const std::vector<int> &order)
     std::vector<double> src;
     if (c->d_src) {
         src.resize((size_t)ne * 3 * c->K);
-        const swe_status st = download(c, c->d_src, 3, src.data(), false);
+        const swe_status st = download(c, c->d_src, 3, src.data());
         if (st) return st;
     }
     std::vector<int> e_perm(ne), ev((size_t)3 * S, 0), nb((size_t)3 * S, NB_LAND);
@@ -943,9 +950,13 @@ swe_status relayout(swe_ctx *c, const std::vector<int> &order)
     HIP_TRY(c, h2d(c, c->d_ev, c->ev.data(), sizeof(int) * 3 * S));
     HIP_TRY(c, h2d(c, c->d_nb, c->nb_host.data(), sizeof(int) * 3 * S));
     HIP_TRY(c, h2d(c, c->d_nbk, c->nbk_host.data(), S));
+    HIP_TRY(c, h2d(c, c->d_iperm, c->e_iperm.data(), sizeof(int) * ne));
     swe_status st = build_items(c);
     if (st) return st;
-    if (c->d_src) st = upload_state(c, src.data(), c->d_src);
+    if (c->d_src) {
+        st = upload_order(c);   // the upload drops modes by the device's order map
+        if (!st) st = upload_state(c, src.data(), c->d_src);
+    }
     return st;
 }
 
@@ -997,12 +1008,12 @@ swe_status group_by_lists(swe_ctx *c)
 }
 
 // Device bytes of the arrays a context keeps as long as it has a mesh: vertex
-// and neighbour ids, neighbour edges, orders, vertices, flag, clock, mass
-// reduction scratch.
+// and neighbour ids, neighbour edges, orders, caller's numbering, vertices,
+// flags, clock, mass reduction scratch.
 int64_t kept_bytes(int64_t ne, int64_t nv)
 {
     const int64_t S = (ne + BLOCK - 1) / BLOCK * BLOCK;
-    return 2 * 3 * 4 * S + 2 * S + 32 * nv + 4 + (int64_t)sizeof(InstDesc) + 8 * (S / BLOCK + 2);
+    return 2 * 3 * 4 * S + 2 * S + 4 * S + 32 * nv + 8 + (int64_t)sizeof(InstDesc) + 8 * (S / BLOCK + 2);
 }
 
 // Device bytes of a context's state: C0, C1, U0, U1, the right-hand-side
@@ -1258,6 +1269,7 @@ swe_status swe_set_mesh(swe_ctx *c, int64_t nv, const double *vxy, int64_t ne, c
     HIP_TRY(c, hipMalloc(&c->d_nb, sizeof(int) * 3 * S));
     HIP_TRY(c, hipMalloc(&c->d_nbk, S));
     HIP_TRY(c, hipMalloc(&c->d_p, S));
+    HIP_TRY(c, hipMalloc(&c->d_iperm, sizeof(int) * S));
     for (int b = 0; b < 2; ++b) {
         HIP_TRY(c, hipMalloc(&c->d_C[b], w * 3 * K * S));
         HIP_TRY(c, hipMalloc(&c->d_U[b], w * 2 * K * S));
@@ -1265,7 +1277,7 @@ swe_status swe_set_mesh(swe_ctx *c, int64_t nv, const double *vxy, int64_t ne, c
         HIP_TRY(c, dzero(c, c->d_U[b], w * 2 * K * S));
     }
     HIP_TRY(c, hipMalloc(&c->d_L, w * 3 * K * S));
-    HIP_TRY(c, hipMalloc(&c->d_flag, sizeof(int)));
+    HIP_TRY(c, hipMalloc(&c->d_flag, 2 * sizeof(int)));   // failure flag; bad value in an upload
     HIP_TRY(c, hipMalloc(&c->d_inst, sizeof(InstDesc)));
     HIP_TRY(c, dzero(c, c->d_flag, sizeof(int)));
     HIP_TRY(c, hipMalloc(&c->d_part, sizeof(double) * (mass_partials((int)ne) + 1)));
@@ -1273,6 +1285,7 @@ swe_status swe_set_mesh(swe_ctx *c, int64_t nv, const double *vxy, int64_t ne, c
     HIP_TRY(c, h2d(c, c->d_ev, c->ev.data(), sizeof(int) * 3 * S));
     HIP_TRY(c, h2d(c, c->d_nb, nb.data(), sizeof(int) * 3 * S));
     HIP_TRY(c, h2d(c, c->d_nbk, nbk.data(), S));
+    HIP_TRY(c, h2d(c, c->d_iperm, c->e_iperm.data(), sizeof(int) * ne));
     c->nb_host = nb;
     c->nbk_host = nbk;
     c->grouped = false;
@@ -1379,8 +1392,10 @@ swe_status swe_set_state(swe_ctx *c, double t0, const double *coef)
     if (!c->have_mesh) return fail(c, SWE_EINVAL, "set_mesh first");
     HIP_TRY(c, hipStreamSynchronize(c->s_base));
     HIP_TRY(c, hipStreamSynchronize(c->s_corr));
-    swe_status st = upload_state(c, coef, c->d_C[0]);
+    // through buffer 1, so that a refused state leaves the current one as it is
+    swe_status st = upload_state(c, coef, c->d_C[1]);
     if (st) return st;
+    HIP_TRY(c, hipMemcpyAsync(c->d_C[0], c->d_C[1], c->rsz * 3 * c->K * c->stride, hipMemcpyDeviceToDevice, c->s_base));
     // modes above each element's order are zero in every state buffer
     HIP_TRY(c, dzero(c, c->d_C[1], c->rsz * 3 * c->K * c->stride));
     HIP_TRY(c, dzero(c, c->d_U[1], c->rsz * 2 * c->K * c->stride));
@@ -1441,9 +1456,16 @@ swe_status swe_set_source(swe_ctx *c, const double *coef)
         c->d_src = nullptr;
         return SWE_OK;
     }
-    if (!c->d_src) HIP_TRY(c, hipMalloc(&c->d_src, c->rsz * 3 * c->K * c->stride));
-    // a right-hand-side coefficient scales like the state
-    return upload_state(c, coef, c->d_src);
+    // a right-hand-side coefficient scales like the state; through buffer 1, so
+    // that a refused source leaves the context as it is
+    const size_t bytes = c->rsz * 3 * c->K * c->stride;
+    swe_status st = upload_state(c, coef, c->d_C[1]);
+    if (st) return st;
+    if (!c->d_src) HIP_TRY(c, hipMalloc(&c->d_src, bytes));
+    HIP_TRY(c, hipMemcpyAsync(c->d_src, c->d_C[1], bytes, hipMemcpyDeviceToDevice, c->s_base));
+    HIP_TRY(c, dzero(c, c->d_C[1], bytes));
+    HIP_TRY(c, hipStreamSynchronize(c->s_base));
+    return SWE_OK;
 }
 
 swe_status swe_step(swe_ctx *c, int64_t nsteps, double dt)
@@ -1519,6 +1541,7 @@ swe_status swe_sync(swe_ctx *c)
 
 swe_status swe_batch_sync(swe_batch *b);
 double batch_member_time(swe_batch *b, int slot);
+swe_status batch_member_state(swe_batch *b, int slot, double *coef, double *t_out);
 
 swe_status swe_get_state(swe_ctx *c, double *coef, double *t_out)
 {
@@ -1527,14 +1550,14 @@ swe_status swe_get_state(swe_ctx *c, double *coef, double *t_out)
     if (c->batch) {
         swe_status st = swe_batch_sync(c->batch);
         if (st != SWE_OK && st != SWE_ESTATE) return fail(c, st, "batch sync failed");
-        c->t = batch_member_time(c->batch, c->slot);   // re-creates the state buffers for the copy
-        if (!c->d_C[0]) return fail(c, SWE_EDEVICE, "state of the resident member could not be read");
+        st = batch_member_state(c->batch, c->slot, coef, &c->t);
+        if (t_out) *t_out = c->t;
+        return st;
     }
     HIP_TRY(c, hipStreamSynchronize(c->s_base));
     HIP_TRY(c, hipStreamSynchronize(c->s_corr));
-    swe_status st = download(c, c->d_C[0], 3, coef, false);
+    swe_status st = download(c, c->d_C[0], 3, coef);
     if (t_out) *t_out = c->t;
-    if (c->batch) release_state_buffers(c);   // while resident the pool holds the state
     return st;
 }
 
@@ -1580,7 +1603,7 @@ swe_status swe_rhs(swe_ctx *c, double t, const double *coef, double *rhs)
                            : enqueue_stage<double>(c, MODE_RHS, 1, -1, t, 0.0, nullptr, c->d_L);
     if (e != hipSuccess) return fail(c, SWE_EDEVICE, std::string("rhs launch: ") + hipGetErrorString(e));
     HIP_TRY(c, hipStreamSynchronize(c->s_base));
-    return download(c, c->d_L, 3, rhs, true);
+    return download_scratch(c, c->d_L, rhs);
 }
 
 swe_status swe_usolve(swe_ctx *c, const double *coef, double *u_out)
@@ -1593,7 +1616,7 @@ swe_status swe_usolve(swe_ctx *c, const double *coef, double *u_out)
     if (st) return st;
     HIP_TRY(c, usolve_buf(c, 1));
     HIP_TRY(c, hipStreamSynchronize(c->s_base));
-    return download(c, c->d_U[1], 2, u_out, false);
+    return download(c, c->d_U[1], 2, u_out);
 }
 
 swe_status swe_rhs_split(swe_ctx *c, double t, const double *coef, double *base_out, double *corr_out)
@@ -1611,9 +1634,9 @@ swe_status swe_rhs_split(swe_ctx *c, double t, const double *coef, double *base_
     hipError_t e = c->fp32 ? enqueue_rhs_split<float>(c, t) : enqueue_rhs_split<double>(c, t);
     if (e != hipSuccess) return fail(c, SWE_EDEVICE, std::string("split rhs launch: ") + hipGetErrorString(e));
     HIP_TRY(c, hipStreamSynchronize(c->s_base));
-    st = download(c, c->d_L, 3, base_out, true);
+    st = download_scratch(c, c->d_L, base_out);
     if (st) return st;
-    return download(c, c->d_Lc, 3, corr_out, true);
+    return download(c, c->d_Lc, 3, corr_out);
 }
 
 swe_status swe_indicator(swe_ctx *c, double t, const double *coef, double *I_out)
@@ -2100,6 +2123,26 @@ double batch_member_time(swe_batch *b, int slot)
     if (get_desc(b, slot) != SWE_OK) return 0.0;
     if (pull_state(b, slot) != SWE_OK) return b->h_inst[slot].t;
     return b->h_inst[slot].t;
+}
+
+// State and time of the resident member in slot, read straight from its pool:
+// no state buffer of the member is re-created, a staging buffer of the
+// caller's layout lives for the call.
+swe_status batch_member_state(swe_batch *b, int slot, double *coef, double *t_out)
+{
+    const swe_batch::Member &m = b->mem[slot];
+    swe_ctx *c = m.ctx;
+    const swe_batch::Pool &P = b->pool[m.order];
+    if (get_desc(b, slot) != SWE_OK) return fail(c, SWE_EDEVICE, b->err);
+    *t_out = b->h_inst[slot].t;
+    if (m.adapt)   // the orders the indicator chose while resident
+        HIP_TRY(c, hipMemcpyAsync(c->d_p, P.v.ep + m.first, c->ne, hipMemcpyDeviceToDevice, c->s_base));
+    const size_t bytes = sizeof(double) * 3 * (size_t)c->K * (size_t)c->ne;
+    void *st = nullptr;
+    HIP_TRY(c, hipMalloc(&st, bytes));
+    const swe_status r = download(c, P.v.C0, P.v.cap, (int)m.first, 3, coef, st, bytes);
+    (void)hipFree(st);
+    return r;
 }
 
 extern "C" {

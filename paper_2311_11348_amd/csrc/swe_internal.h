@@ -172,6 +172,16 @@ hipError_t launch_epi_all(int b, int pn, bool fp32, int mode, const void *args, 
 int host_corr(int b, int pn, bool fp32, const void *args, double dt, const signed char *order, int e0, int e1,
               int nthreads);
 hipError_t launch_usolve(int p, bool fp32, const void *args, hipStream_t s);
+// State in and out: the caller's elements [u0, u1) between FP64 coefficients
+// [element][slot] (in / out hold those elements only) and the device's
+// reference-scaled arrays; iperm: caller's element -> index, first: offset of
+// the indices in src (a batch's pool), ev / evs: vertex ids and their stride.
+// unpack reads each element's order from m.ep and sets bad[0] on a non-finite
+// value of a kept mode.
+hipError_t launch_pack(bool fp32, const void *src, int stride, int first, int nslots, const int *iperm,
+                       const double4 *vtx, const int *ev, int evs, int u0, int u1, double *out, hipStream_t s);
+hipError_t launch_unpack(bool fp32, const double *in, int K, const int *iperm, const MeshView &m, int u0, int u1,
+                         void *dst, int *bad, hipStream_t s);
 // minimum depth control over every element of the stage output (args.Cout,
 // args.Uout; per-element orders from args.m.ep, at most pm)
 hipError_t launch_depth_limit(int pm, bool fp32, const void *args, double h_min, Sink &k);
