@@ -15,7 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT_DIR = os.path.join(HERE, "_lib")
 LIB = os.path.join(OUT_DIR, "libswe_hip.so")
-SOURCES = ["swe_kernels.hip", "swe_api.cpp"]
+SOURCES = ["swe_kernels.hip", "swe_step.hip", "swe_api.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-Wall", "-Wno-unused-function",
@@ -39,16 +39,18 @@ def regenerate_tables() -> None:
 def build(verbose: bool = False) -> str:
     os.makedirs(OUT_DIR, exist_ok=True)
     regenerate_tables()
-    objs = []
-    for src in SOURCES:
+    objs, jobs = [], []
+    for src in SOURCES:                      # one compiler per source, side by side
         obj = os.path.join(OUT_DIR, os.path.splitext(src)[0] + ".o")
         cmd = [HIPCC, *FLAGS, "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
-        r = subprocess.run(cmd, capture_output=True, text=True)
-        if r.returncode != 0:
-            raise RuntimeError(f"hipcc failed for {src}:\n{r.stderr}")
+        jobs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True)))
         objs.append(obj)
+    ended = [(src, j.communicate()[1], j.returncode) for src, j in jobs]
+    failed = [(src, err) for src, err, rc in ended if rc != 0]
+    if failed:
+        raise RuntimeError("\n".join(f"hipcc failed for {src}:\n{err}" for src, err in failed))
     tmp = LIB + ".tmp"
     cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", *objs, "-o", tmp]
     r = subprocess.run(cmd, capture_output=True, text=True)

@@ -37,6 +37,7 @@ constexpr double QPHI[SWET_NQP][10] = SWET_QPHI;
 struct swe_ctx {
     swe_config cfg{};
     bool fp32 = false;
+    int ncu = 256;
     int K = 1;
     size_t rsz = 8;
     int64_t ne = 0, nv = 0;
@@ -91,6 +92,8 @@ struct swe_ctx {
     unsigned *d_items = nullptr;           // edge items of the shared-flux stage kernel, per block
     int *d_item_off = nullptr;            // [blocks + 1]
     int64_t item_blocks = 0;              // the leading blocks whose items are built
+    void *d_tiles = nullptr;              // tile data of the one-launch step (one allocation)
+    TileView tiles{};                     // its arrays; len 0: none
     InstDesc *d_inst = nullptr;
     hipGraph_t step_graph = nullptr, multi_graph = nullptr;   // one step; GRAPH_STEPS steps
     hipGraphExec_t step_exec = nullptr, multi_exec = nullptr;
@@ -144,6 +147,13 @@ void drop_step_graph(swe_ctx *c)
     c->graph_key.clear();
 }
 
+void free_tiles(swe_ctx *c)
+{
+    if (c->d_tiles) (void)hipFree(c->d_tiles);
+    c->d_tiles = nullptr;
+    c->tiles = TileView{};
+}
+
 void free_mesh(swe_ctx *c)
 {
     drop_step_graph(c);
@@ -153,6 +163,7 @@ void free_mesh(swe_ctx *c)
     if (c->d_item_off) (void)hipFree(c->d_item_off);
     c->d_items = nullptr;
     c->d_item_off = nullptr;
+    free_tiles(c);
     void *ptrs[] = {c->d_vtx, c->d_ev, c->d_nb, c->d_nbk, c->d_p, c->d_iperm, c->d_C[0], c->d_C[1],
                     c->d_U[0], c->d_U[1], c->d_L, c->d_src, c->d_flag, c->d_part, c->d_mass,
                     c->d_inlist, c->d_Lb, c->d_Lc, c->d_list, c->d_cnt, c->d_pnew, c->d_I};
@@ -173,7 +184,7 @@ void free_mesh(swe_ctx *c)
 }
 
 // A batch member's state buffers (C0, C1, U0, U1, the right-hand-side
-// scratch, edge items) are released while it is resident: its state lives in
+// scratch, edge items, tiles) are released while it is resident: its state lives in
 // the batch's pool.  They are re-created (zero-filled) when the state comes
 // back; the edge items when the member leaves the batch.
 void release_state_buffers(swe_ctx *c)
@@ -186,6 +197,7 @@ void release_state_buffers(swe_ctx *c)
     c->d_items = nullptr;
     c->d_item_off = nullptr;
     c->item_blocks = 0;
+    free_tiles(c);
 }
 
 swe_status restore_state_buffers(swe_ctx *c)
@@ -339,6 +351,28 @@ hipError_t enqueue_stage(swe_ctx *c, int mode, int in, int out, double tstage, d
 }
 
 bool separated(const swe_ctx *c) { return c->cfg.separate && c->cfg.p_base < c->cfg.p_max; }
+
+// Both stages of a step in one launch: the fused scheme on a uniform order
+// with nothing between the stages.  A call's steps run in pairs (state buffer
+// 0 -> 1 -> 0), so the state rests in buffer 0 as ever; the last of an odd
+// number takes two stage launches.
+bool one_launch_steps(const swe_ctx *c)
+{
+    return c->tiles.len > 0 && c->uniform && !separated(c) && !c->cfg.adapt && !(c->cfg.h_min > 0.0);
+}
+
+template <typename Real>
+hipError_t enqueue_one_launch_step(Lanes &L, int in, double tn, double dt)
+{
+    swe_ctx *c = L.c;
+    StageArgs<Real> a = make_args<Real>(c);
+    a.Cin = static_cast<const Real *>(c->d_C[in]);
+    a.Uin = static_cast<const Real *>(c->d_U[in]);
+    a.Cout = static_cast<Real *>(c->d_C[1 - in]);
+    a.Uout = static_cast<Real *>(c->d_U[1 - in]);
+    L.time(a, 0, tn, dt);
+    return launch_step_sh(c->cfg.p_max, c->fp32, &a, c->tiles, L.graph ? 0.0 : xi_hat(c, tn + dt), L.a);
+}
 
 // Base pass of the order-separated and order-partitioned schemes over the
 // elements [0, end): the shared-flux kernel at the base order (orders 1..3)
@@ -600,6 +634,13 @@ hipError_t enqueue_step(Lanes &L, double tn, double dt)
     return e;
 }
 
+// Step s of a call whose first `paired` steps take one launch each.
+template <typename Real>
+hipError_t enqueue_step_of(Lanes &L, int64_t s, int64_t paired, double tn, double dt)
+{
+    return s < paired ? enqueue_one_launch_step<Real>(L, (int)(s & 1), tn, dt) : enqueue_step<Real>(L, tn, dt);
+}
+
 // The step graph: the device clock (stage times, open-sea elevation, depth
 // check stop; an adaptive step's order update advances it), then one step as
 // above.  Rebuilt when what it launches changes.
@@ -619,10 +660,12 @@ hipError_t build_graph(swe_ctx *c, int nsteps, hipGraph_t *g_out, hipGraphExec_t
     hipError_t e = hipGraphCreate(&g, 0);
     if (e != hipSuccess) return e;
     Lanes L(c, g);
+    const int paired = one_launch_steps(c) ? nsteps / 2 * 2 : 0;
     for (int s = 0; s < nsteps && e == hipSuccess; ++s) {
         // an adaptive step's order update advances the clock itself
         if (!c->cfg.adapt) e = launch_batch_clock(c->d_inst, c->d_flag, 1, L.a);
-        if (e == hipSuccess) e = c->fp32 ? enqueue_step<float>(L, 0.0, 0.0) : enqueue_step<double>(L, 0.0, 0.0);
+        if (e == hipSuccess) e = c->fp32 ? enqueue_step_of<float>(L, s, paired, 0.0, 0.0)
+                                         : enqueue_step_of<double>(L, s, paired, 0.0, 0.0);
     }
     if (e == hipSuccess) e = hipGraphInstantiate(x_out, g, nullptr, nullptr, 0);
     if (e != hipSuccess) {
@@ -803,6 +846,60 @@ hipError_t enqueue_rhs_split(swe_ctx *c, double t)
     return e;
 }
 
+// One launch per step pays when its tiles do not need many more rounds of
+// resident blocks than the 256-element blocks of two launches.  Kernels with
+// three or more blocks per CU (order 1, FP32 order 2) win at every size
+// (measured from 7,200 to 524,288 elements: 1.02-1.46x).  With two blocks per
+// CU a tile takes about 1.5 times a stage block (FP64 p = 2: 96,800 elements,
+// two rounds against one, 44.9 against 40.2 us a step; 156,800, two against
+// two, 57 against 65; 524,288, six against four, 142 against 158); FP64 p = 3
+// runs one block per CU and takes 1.35-1.6 times (45,000 elements, one round each,
+// 38 against 49 us; 65,522, two against one, 74 against 56; 192,200, five
+// against three, 184 against 160; 231,200, five against four, 189 against 203).
+bool one_launch_pays(const swe_ctx *c, int len)
+{
+    const int p = c->cfg.p_max;
+    const int per_cu = c->fp32 ? (p == 3 ? 2 : 0) : (p == 2 ? 2 : p == 3 ? 1 : 0);
+    if (per_cu == 0) return true;
+    const int64_t slots = (int64_t)per_cu * c->ncu;
+    const int64_t tiles = (c->ne + len - 1) / len, blocks = (c->ne + BLOCK - 1) / BLOCK;
+    const int64_t rt = (tiles + slots - 1) / slots, rb = (blocks + slots - 1) / slots;
+    return per_cu == 1 ? 5 * rt < 7 * rb : 2 * rt <= 3 * rb;
+}
+
+// Tiles of the one-launch step for the current numbering (replacing any built
+// before), by a device kernel: 192 owned elements each (three waves, the ring
+// in the fourth), or fewer, by eights, where some tile of the mesh is beyond a
+// block (a ring above 64 elements, many boundary edges); below 128 owned
+// elements the ring costs as much as they do, and the mesh keeps two launches
+// per step.
+swe_status build_tiles(swe_ctx *c)
+{
+    free_tiles(c);
+    if (separated(c) || c->cfg.adapt || c->cfg.h_min > 0.0 || !stage_sh_supported(c->cfg.p_max, c->fp32)) return SWE_OK;
+    for (int len = 192; len >= 128 && one_launch_pays(c, len);) {
+        const size_t nt = (size_t)((c->ne + len - 1) / len);
+        HIP_TRY(c, hipMalloc(&c->d_tiles, nt * TILE_BYTES));
+        TileView t{};
+        t.items = static_cast<unsigned *>(c->d_tiles);
+        t.meta = reinterpret_cast<int *>(t.items + nt * 2 * BLOCK);
+        t.tri = reinterpret_cast<unsigned *>(t.meta + nt * BLOCK);
+        t.verts = reinterpret_cast<int *>(t.tri + nt * BLOCK);
+        t.len = len;
+        int over[2] = {0, 0};
+        HIP_TRY(c, dzero(c, c->d_flag + 1, sizeof(over)));
+        HIP_TRY(c, launch_build_tiles(view(c), (int)c->ne, t, c->d_flag + 1, c->s_base));
+        HIP_TRY(c, d2h(c, over, c->d_flag + 1, sizeof(over)));
+        if (!over[0] && !over[1]) {
+            c->tiles = t;
+            return SWE_OK;
+        }
+        free_tiles(c);
+        len -= std::max(8, over[0] / 8 * 8);
+    }
+    return SWE_OK;
+}
+
 #ifndef SWE_SHARED_FLUX
 #define SWE_SHARED_FLUX 1
 #endif
@@ -814,6 +911,7 @@ hipError_t enqueue_rhs_split(swe_ctx *c, double t)
 // blocks hold many edges to outside); else none.
 swe_status build_items(swe_ctx *c)
 {
+    if (swe_status st = build_tiles(c)) return st;
     if (c->d_items) (void)hipFree(c->d_items);
     if (c->d_item_off) (void)hipFree(c->d_item_off);
     c->d_items = nullptr;
@@ -1013,17 +1111,18 @@ swe_status group_by_lists(swe_ctx *c)
 int64_t kept_bytes(int64_t ne, int64_t nv)
 {
     const int64_t S = (ne + BLOCK - 1) / BLOCK * BLOCK;
-    return 2 * 3 * 4 * S + 2 * S + 4 * S + 32 * nv + 8 + (int64_t)sizeof(InstDesc) + 8 * (S / BLOCK + 2);
+    return 2 * 3 * 4 * S + 2 * S + 4 * S + 32 * nv + 12 + (int64_t)sizeof(InstDesc) + 8 * (S / BLOCK + 2);
 }
 
 // Device bytes of a context's state: C0, C1, U0, U1, the right-hand-side
-// scratch and the shared-flux kernel's edge items (at most 3 per element).
+// scratch, the shared-flux kernel's edge items (at most 3 per element) and the
+// tiles of the one-launch step (at least 128 elements each).
 int64_t state_bytes(int64_t ne, int p, bool fp32)
 {
     const int64_t S = (ne + BLOCK - 1) / BLOCK * BLOCK;
     const int64_t K = K_OF[p], w = fp32 ? 4 : 8;
     int64_t b = (2 * 3 * K + 2 * 2 * K + 3 * K) * S * w;
-    if (stage_sh_supported(p, fp32)) b += 3 * 4 * S + 4 * (S / BLOCK + 1);
+    if (stage_sh_supported(p, fp32)) b += 3 * 4 * S + 4 * (S / BLOCK + 1) + (int64_t)TILE_BYTES * ((S + 127) / 128);
     return b;
 }
 
@@ -1085,6 +1184,10 @@ swe_status swe_create(const swe_config *cfg, swe_ctx **out)
     c->fp32 = cfg->precision == SWE_FP32_WB;
     c->rsz = c->fp32 ? 4 : 8;
     c->K = K_OF[cfg->p_max];
+    int dev = 0, ncu = 0;
+    if (hipGetDevice(&dev) == hipSuccess &&
+        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && ncu > 0)
+        c->ncu = ncu;
     if (cfg->stream_base) {
         c->s_base = static_cast<hipStream_t>(cfg->stream_base);
     } else {
@@ -1277,7 +1380,7 @@ swe_status swe_set_mesh(swe_ctx *c, int64_t nv, const double *vxy, int64_t ne, c
         HIP_TRY(c, dzero(c, c->d_U[b], w * 2 * K * S));
     }
     HIP_TRY(c, hipMalloc(&c->d_L, w * 3 * K * S));
-    HIP_TRY(c, hipMalloc(&c->d_flag, 2 * sizeof(int)));   // failure flag; bad value in an upload
+    HIP_TRY(c, hipMalloc(&c->d_flag, 3 * sizeof(int)));   // failure flag; two words for transfers and set-up
     HIP_TRY(c, hipMalloc(&c->d_inst, sizeof(InstDesc)));
     HIP_TRY(c, dzero(c, c->d_flag, sizeof(int)));
     HIP_TRY(c, hipMalloc(&c->d_part, sizeof(double) * (mass_partials((int)ne) + 1)));
@@ -1514,9 +1617,11 @@ swe_status swe_step(swe_ctx *c, int64_t nsteps, double dt)
         return SWE_OK;
     }
     Lanes L(c);
+    const int64_t paired = one_launch_steps(c) ? nsteps / 2 * 2 : 0;
     for (int64_t s = 0; s < nsteps; ++s) {
         const double tn = t0 + (double)s * dt;
-        const hipError_t e = c->fp32 ? enqueue_step<float>(L, tn, dt) : enqueue_step<double>(L, tn, dt);
+        const hipError_t e = c->fp32 ? enqueue_step_of<float>(L, s, paired, tn, dt)
+                                     : enqueue_step_of<double>(L, s, paired, tn, dt);
         if (e != hipSuccess) return fail(c, SWE_EDEVICE, std::string("stage launch: ") + hipGetErrorString(e));
         c->t = t0 + (double)(s + 1) * dt;
     }

@@ -19,6 +19,13 @@ constexpr int NB_OPEN = -2;
 // (it aligns the next kind of item to a wave of 64 lanes).
 constexpr unsigned ITEM_PAD = 0xffffffffu;
 
+// In the tiles of the one-launch step: an edge item that touches no owned
+// element of its tile (first stage only).
+constexpr unsigned ITEM_RING = 1u << 22;
+// Vertices a tile may have (256 triangles of a planar region with few holes
+// have at most about 180).
+constexpr int TILE_NV = 192;
+
 enum StageMode { MODE_RHS = 0, MODE_STAGE1 = 1, MODE_STAGE2 = 2 };
 
 struct Physics {
@@ -79,6 +86,17 @@ struct StageArgs {
     int skip_listed;     // base kernel of the order-partitioned scheme: listed elements are not its work
     int blocks;          // stage launchers: cover the first blocks * BLOCK elements only (0: all)
 };
+
+// Tiles of the one-launch step (see k_step_sh): tile t owns the len elements
+// from t * len on; a fixed-size record in each array.
+struct TileView {
+    unsigned *items;     // [2 * BLOCK] edge items
+    int *meta;           // [BLOCK] owned slots: outside neighbours' ids; then the ring's element ids, -1 past them
+    unsigned *tri;       // [BLOCK] local vertex numbers, 8 bits each
+    int *verts;          // [TILE_NV] vertex ids, -1 past them
+    int len;             // owned elements per tile; 0: no tiles
+};
+constexpr size_t TILE_BYTES = 4 * (2 * (size_t)BLOCK + BLOCK + BLOCK + TILE_NV);
 
 struct InstDesc;
 
@@ -158,6 +176,12 @@ hipError_t launch_stage(int p, bool fp32, int mode, bool sep, const void *args, 
 bool stage_sh_supported(int p, bool fp32);
 hipError_t launch_stage_sh(int p, bool fp32, int mode, const void *args, const unsigned *items, const int *item_off,
                            Sink &k);
+// both stages of a step in one launch (orders 1 to 3, uniform); args as for a
+// first stage, xihat2 the open-sea elevation of the second
+hipError_t launch_step_sh(int p, bool fp32, const void *args, const TileView &tv, double xihat2, Sink &k);
+// tile data of the mesh's tiles; over[0]: lanes by which the fullest is beyond
+// a block, over[1]: set if some tile does not fit for another reason
+hipError_t launch_build_tiles(const MeshView &m, int ne, const TileView &tv, int *over, hipStream_t s);
 // The listed elements of every order in one launch (orders lo..pn, nblk
 // blocks per order; lists at args.list + p * lcap, lengths args.count[p]):
 // full stage (order-partitioned scheme), correction and epilogue (order-
