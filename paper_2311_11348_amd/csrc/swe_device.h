@@ -875,18 +875,27 @@ constexpr bool batch_sh_fp32p3()
 // words, no bank conflicts), and slot[k][l] tells element l which item
 // holds its local edge k (bit 15: l is the item's second side, which sees
 // the flux negated and reversed along the edge).
-template <int P, typename Real>
+// With BOTH the two have storage of their own: fluxes are then written as
+// they are computed, and the next state copy while they are still needed, with
+// half the barriers.
+template <int P, typename Real, bool BOTH = false>
 struct ShLds {
     static constexpr int K = Ord<P>::K, NT = Ord<P>::NT;
     Real R[3][K][NT];              // trace matrices
     unsigned short slot[3][BLOCK]; // item of each (local edge, element)
-    union {
+    struct Fluxes {
+        Real F[3 * NT][2 * BLOCK];  // flux modes (component, mode) per item
+        double W[NT][2 * BLOCK];    // bathymetry part of the pressure flux, FP64, per item
+    };
+    union Shared {
         Real C[5 * K][BLOCK];      // xi, U, V, u, v modes of the block's elements
-        struct {
-            Real F[3 * NT][2 * BLOCK];  // flux modes (component, mode) per item
-            double W[NT][2 * BLOCK];    // bathymetry part of the pressure flux, FP64, per item
-        } E;
-    } U;
+        Fluxes E;
+    };
+    struct Apart {
+        Real C[5 * K][BLOCK];
+        Fluxes E;
+    };
+    std::conditional_t<BOTH, Apart, Shared> U;
 };
 
 // An edge item's results, kept in registers until the state copy is no
@@ -898,8 +907,8 @@ struct ShItem {
     double W[NT];
 };
 
-template <int P, typename Real>
-__device__ __forceinline__ void traces_of(const ShLds<P, Real> &S, int l, int k, Real (&t)[5][Ord<P>::NT])
+template <int P, typename Real, bool BOTH>
+__device__ __forceinline__ void traces_of(const ShLds<P, Real, BOTH> &S, int l, int k, Real (&t)[5][Ord<P>::NT])
 {
     constexpr int K = Ord<P>::K, NT = Ord<P>::NT;
 #pragma unroll
@@ -916,11 +925,11 @@ __device__ __forceinline__ void traces_of(const ShLds<P, Real> &S, int l, int k,
         }
 }
 
-template <int P, typename Real>
-__device__ __forceinline__ void load_trace_lds(ShLds<P, Real> &S)
+template <int P, typename Real, bool BOTH>
+__device__ __forceinline__ void load_trace_lds(ShLds<P, Real, BOTH> &S)
 {
     constexpr int K = Ord<P>::K, NT = Ord<P>::NT;
-    for (int i = threadIdx.x; i < 3 * K * NT; i += BLOCK) {
+    for (int i = threadIdx.x; i < 3 * K * NT; i += (int)blockDim.x) {
         const int k = i / (K * NT), r = i % (K * NT);
         S.R[k][r / NT][r % NT] = Real(TR[k][r / NT][r % NT]);
     }
@@ -955,8 +964,8 @@ struct BlockSrc {
 // times two (its factor 1/2 is applied with dt / |det B| at the lift) and
 // unscaled by dt / |det B| (the edge pass of the shared-flux kernels); the
 // FP64 bathymetry part W is complete.
-template <int P, typename Real, typename Src>
-__device__ __forceinline__ void sh_flux(const ShLds<P, Real> &S, int KS, const Buf<Real> &bC, const Buf<Real> &bU,
+template <int P, typename Real, bool BOTH, typename Src>
+__device__ __forceinline__ void sh_flux(const ShLds<P, Real, BOTH> &S, int KS, const Buf<Real> &bC, const Buf<Real> &bU,
                                         const Src &src, unsigned w, double xihat, double g, ShItem<P, Real> &out)
 {
     constexpr int K = Ord<P>::K, NT = Ord<P>::NT;
@@ -971,7 +980,7 @@ __device__ __forceinline__ void sh_flux(const ShLds<P, Real> &S, int KS, const B
     const double hmid = 0.5 * (pa.z + pb.z);
     const double hbt[2] = {hmid, (pb.z - pa.z) * INV_2SQRT3};
     Real tm[5][NT], tp[5][NT];
-    traces_of<P, Real>(S, la, ka, tm);
+    traces_of<P, Real, BOTH>(S, la, ka, tm);
     const Real xbm = Real(SQRT2) * S.U.C[0][la];
     const Real unbm = fabs(fma(Real(SQRT2) * S.U.C[3 * K][la], nx, Real(SQRT2) * S.U.C[4 * K][la] * ny));
     Real unm[NT], qnm[NT], unp[NT], qnp[NT];
@@ -984,7 +993,7 @@ __device__ __forceinline__ void sh_flux(const ShLds<P, Real> &S, int KS, const B
     if (kind == EK_PAIR || kind == EK_EXT) {
         Real x0, u0, v0;
         if (kind == EK_PAIR) {
-            traces_of<P, Real>(S, lb, kb, tp);
+            traces_of<P, Real, BOTH>(S, lb, kb, tp);
             x0 = S.U.C[0][lb];
             u0 = S.U.C[3 * K][lb];
             v0 = S.U.C[4 * K][lb];
@@ -1085,8 +1094,8 @@ __device__ __forceinline__ void sh_flux(const ShLds<P, Real> &S, int KS, const B
 
 // Store item i's flux in its column and point its sides' slots at it (the
 // second side of a pair inside the block marked by bit 15).
-template <int P, typename Real>
-__device__ __forceinline__ void sh_store(ShLds<P, Real> &S, int i, unsigned w, const ShItem<P, Real> &r)
+template <int P, typename Real, bool BOTH>
+__device__ __forceinline__ void sh_store(ShLds<P, Real, BOTH> &S, int i, unsigned w, const ShItem<P, Real> &r)
 {
     constexpr int NT = Ord<P>::NT;
     const int la = (int)(w & 255u), ka = (int)((w >> 8) & 3u), lb = (int)((w >> 10) & 255u);
@@ -1103,8 +1112,8 @@ __device__ __forceinline__ void sh_store(ShLds<P, Real> &S, int i, unsigned w, c
 
 // Lift element l's three edge fluxes from the block's item columns onto its
 // modes, with its own geometry.
-template <int P, typename Real>
-__device__ __forceinline__ void sh_lift(const ShLds<P, Real> &S, const Geo &G, int l, double dt, Acc<P, Real> &A)
+template <int P, typename Real, bool BOTH>
+__device__ __forceinline__ void sh_lift(const ShLds<P, Real, BOTH> &S, const Geo &G, int l, double dt, Acc<P, Real> &A)
 {
     constexpr int K = Ord<P>::K, NT = Ord<P>::NT;
     const double dt_det = dt * G.idet;
@@ -1221,11 +1230,11 @@ __device__ __forceinline__ void stage_sh_block(ShLds<P, Real> &S, const StageArg
     const unsigned w0 = it0 < n ? items[it0] : ITEM_PAD, w1 = it1 < n ? items[it1] : ITEM_PAD;
     ShItem<P, Real> r0, r1;
     const BlockSrc bsrc{m, bEv, bNb, e0};
-    if (w0 != ITEM_PAD) sh_flux<P, Real>(S, KS, bC, bU, bsrc, w0, xihat, g, r0);
-    if (w1 != ITEM_PAD) sh_flux<P, Real>(S, KS, bC, bU, bsrc, w1, xihat, g, r1);
+    if (w0 != ITEM_PAD) sh_flux<P, Real, false>(S, KS, bC, bU, bsrc, w0, xihat, g, r0);
+    if (w1 != ITEM_PAD) sh_flux<P, Real, false>(S, KS, bC, bU, bsrc, w1, xihat, g, r1);
     __syncthreads();
-    if (w0 != ITEM_PAD) sh_store<P, Real>(S, it0, w0, r0);
-    if (w1 != ITEM_PAD) sh_store<P, Real>(S, it1, w1, r1);
+    if (w0 != ITEM_PAD) sh_store<P, Real, false>(S, it0, w0, r0);
+    if (w1 != ITEM_PAD) sh_store<P, Real, false>(S, it1, w1, r1);
     __syncthreads();
     if (!live) return;
     // base pass of the order-partitioned scheme: a listed element belongs to
@@ -1242,7 +1251,7 @@ __device__ __forceinline__ void stage_sh_block(ShLds<P, Real> &S, const StageArg
     acc_init<P, Real>(A, s, MODE != MODE_RHS);
     volume_term<P, Real>(s, hbh, G, g, dt, A);
     source_term<P, Real>(s, G, a.ph, dt, A);
-    sh_lift<P, Real>(S, G, (int)l, dt, A);
+    sh_lift<P, Real, false>(S, G, (int)l, dt, A);
     if constexpr (Acc<P, Real>::SPLIT) {
 #pragma unroll
         for (int q = 0; q < K; ++q) {

@@ -177,8 +177,9 @@ bool stage_sh_supported(int p, bool fp32);
 hipError_t launch_stage_sh(int p, bool fp32, int mode, const void *args, const unsigned *items, const int *item_off,
                            Sink &k);
 // both stages of a step in one launch (orders 1 to 3, uniform); args as for a
-// first stage, xihat2 the open-sea elevation of the second
-hipError_t launch_step_sh(int p, bool fp32, const void *args, const TileView &tv, double xihat2, Sink &k);
+// first stage, xihat2 the open-sea elevation of the second, ncu the device's
+// compute units (a mesh of at most one tile each takes the kernel with roles)
+hipError_t launch_step_sh(int p, bool fp32, const void *args, const TileView &tv, double xihat2, int ncu, Sink &k);
 // tile data of the mesh's tiles; over[0]: lanes by which the fullest is beyond
 // a block, over[1]: set if some tile does not fit for another reason
 hipError_t launch_build_tiles(const MeshView &m, int ne, const TileView &tv, int *over, hipStream_t s);

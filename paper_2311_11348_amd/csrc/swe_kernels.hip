@@ -47,7 +47,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(sh_w
 k_stage_sh(StageArgs<Real> a, const unsigned *items, const int *item_off)
 {
     __shared__ ShLds<P, Real> S;
-    load_trace_lds<P, Real>(S);
+    load_trace_lds<P, Real, false>(S);
     const int blk = xcd_block(blockIdx.x, gridDim.x);
     double xihat = a.xihat, dt = a.dt;
     if (a.inst) {
@@ -206,7 +206,7 @@ __attribute__((amdgpu_waves_per_eu(batch_sh_fp32p3<P, Real>() ? 3 : sh_waves<P, 
 k_batch_stage_sh(BatchArgs b)
 {
     __shared__ ShLds<P, Real> S;
-    load_trace_lds<P, Real>(S);
+    load_trace_lds<P, Real, false>(S);
     // the returns below are uniform over the block (tile and instance)
     const int ntiles = b.ntiles[0];
     const int x = (int)(blockIdx.x & 7u), i = (int)(blockIdx.x >> 3);

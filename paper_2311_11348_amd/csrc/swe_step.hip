@@ -25,16 +25,16 @@ namespace {
 // items, ring and outside neighbours, and the tile's vertices, which are
 // staged in LDS so that neither the edge pass nor the element pass reads
 // vertex ids or vertices from memory.
-template <int P, typename Real>
+template <int P, typename Real, bool BOTH>
 struct StepLds {
-    ShLds<P, Real> S;
+    ShLds<P, Real, BOTH> S;
     double vx[TILE_NV], vy[TILE_NV], vh[TILE_NV];
     unsigned tri[BLOCK];   // an element's three vertices among the tile's, 8 bits each
 };
 
-template <int P, typename Real>
+template <int P, typename Real, bool BOTH>
 struct TileSrc {
-    const StepLds<P, Real> &T;
+    const StepLds<P, Real, BOTH> &T;
     int ext;               // the item's neighbour outside the tile
     __device__ __forceinline__ void edge(int la, int va, int vb, double3 &pa, double3 &pb) const
     {
@@ -50,8 +50,8 @@ struct TileSrc {
     }
 };
 
-template <int P, typename Real>
-__device__ __forceinline__ void sh_copy_state(ShLds<P, Real> &S, int l, const Fields<P, Real> &s)
+template <int P, typename Real, bool BOTH>
+__device__ __forceinline__ void sh_copy_state(ShLds<P, Real, BOTH> &S, int l, const Fields<P, Real> &s)
 {
     constexpr int K = Ord<P>::K;
 #pragma unroll
@@ -64,9 +64,25 @@ __device__ __forceinline__ void sh_copy_state(ShLds<P, Real> &S, int l, const Fi
     }
 }
 
+// geometry of local element l from the tile's vertices
+template <int P, typename Real, bool BOTH>
+__device__ __forceinline__ void tile_geo(const StepLds<P, Real, BOTH> &T, int l, Geo &G)
+{
+    unsigned t = T.tri[l];
+    asm volatile("" : "+v"(t));   // formed anew at each use, not kept in registers between the stages
+#pragma unroll
+    for (int v = 0; v < 3; ++v) {
+        const int i = (int)((t >> (8 * v)) & 255u);
+        G.X[v] = T.vx[i];
+        G.Y[v] = T.vy[i];
+        G.h[v] = T.vh[i];
+    }
+    geo_finish(G);
+}
+
 // One tile, elements [e0, e0 + nown) owned; every thread of the block calls it.
 template <int P, typename Real>
-__device__ __forceinline__ void step_tile(StepLds<P, Real> &T, const StageArgs<Real> &a, const TileView &tv, int tile,
+__device__ __forceinline__ void step_tile(StepLds<P, Real, false> &T, const StageArgs<Real> &a, const TileView &tv, int tile,
                                           unsigned e0, int nown, double xh0, double xh1, double dt0, int *flag)
 {
     constexpr int K = Ord<P>::K;
@@ -98,7 +114,7 @@ __device__ __forceinline__ void step_tile(StepLds<P, Real> &T, const StageArgs<R
     {
         const Buf<Real> bC(a.Cin, 3 * KS0, stride0), bU(a.Uin, 2 * KS0, stride0);
         load_state<P, Real>(bC, bU, KS0, off, s);
-        sh_copy_state<P, Real>(T.S, l, s);
+        sh_copy_state<P, Real, false>(T.S, l, s);
     }
     __syncthreads();
 #pragma unroll
@@ -122,25 +138,16 @@ __device__ __forceinline__ void step_tile(StepLds<P, Real> &T, const StageArgs<R
         const bool use1 = v1 != ITEM_PAD && !(st && (v1 & ITEM_RING));
         {
             ShItem<P, Real> r0, r1;
-            if (use0) sh_flux<P, Real>(T.S, KS, bC, bU, TileSrc<P, Real>{T, x0}, v0, xihat, g, r0);
-            if (use1) sh_flux<P, Real>(T.S, KS, bC, bU, TileSrc<P, Real>{T, x1}, v1, xihat, g, r1);
+            if (use0) sh_flux<P, Real, false>(T.S, KS, bC, bU, TileSrc<P, Real, false>{T, x0}, v0, xihat, g, r0);
+            if (use1) sh_flux<P, Real, false>(T.S, KS, bC, bU, TileSrc<P, Real, false>{T, x1}, v1, xihat, g, r1);
             __syncthreads();
-            if (use0) sh_store<P, Real>(T.S, l, v0, r0);
-            if (use1) sh_store<P, Real>(T.S, l + BLOCK, v1, r1);
+            if (use0) sh_store<P, Real, false>(T.S, l, v0, r0);
+            if (use1) sh_store<P, Real, false>(T.S, l + BLOCK, v1, r1);
         }
         __syncthreads();
         if (st && l >= nown) return;   // (no barrier follows)
         Geo G;
-        unsigned t = T.tri[lx];
-        asm volatile("" : "+v"(t));
-#pragma unroll
-        for (int v = 0; v < 3; ++v) {
-            const int i = (int)((t >> (8 * v)) & 255u);
-            G.X[v] = T.vx[i];
-            G.Y[v] = T.vy[i];
-            G.h[v] = T.vh[i];
-        }
-        geo_finish(G);
+        tile_geo<P, Real, false>(T, lx, G);
         double hbh[3];
         hb_modes(G, hbh);
         Acc<P, Real> A;
@@ -156,7 +163,7 @@ __device__ __forceinline__ void step_tile(StepLds<P, Real> &T, const StageArgs<R
 #pragma unroll
                 for (int q = 0; q < K; ++q) cn[j][q] = bC.ld(j * KS + q, off);
         }
-        sh_lift<P, Real>(T.S, G, lx, dt, A);
+        sh_lift<P, Real, false>(T.S, G, lx, dt, A);
         if constexpr (Acc<P, Real>::SPLIT) {
 #pragma unroll
             for (int q = 0; q < K; ++q) {
@@ -191,7 +198,7 @@ __device__ __forceinline__ void step_tile(StepLds<P, Real> &T, const StageArgs<R
         if (!(Hmean > 0.0) || !isfinite(chk)) flag[0] = 1;
         if (st == 0) {
             __syncthreads();   // every lane is done with the first stage's fluxes
-            sh_copy_state<P, Real>(T.S, l, s);
+            sh_copy_state<P, Real, false>(T.S, l, s);
             __syncthreads();
         }
     }
@@ -212,8 +219,8 @@ template <int P, typename Real>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(step_waves<P, Real>(), 8)))
 k_step_sh(StageArgs<Real> a, TileView tv, double xihat2)
 {
-    __shared__ StepLds<P, Real> T;
-    load_trace_lds<P, Real>(T.S);
+    __shared__ StepLds<P, Real, false> T;
+    load_trace_lds<P, Real, false>(T.S);
     double xh0 = a.xihat, xh1 = xihat2, dt = a.dt;
     if (a.inst) {
         // the step's clock stopped (failure): the whole block leaves before its first barrier
@@ -225,6 +232,161 @@ k_step_sh(StageArgs<Real> a, TileView tv, double xihat2)
     const int tile = xcd_block(blockIdx.x, gridDim.x);
     const int e0 = tile * tv.len, left = a.m.ne - e0;
     step_tile<P, Real>(T, a, tv, tile, (unsigned)e0, left < tv.len ? left : tv.len, xh0, xh1, dt, a.flag);
+}
+
+// The same tile by groups of four waves with roles: NG groups compute the edge
+// fluxes (two items per lane, or one with NG = 2) while the first group does
+// the volume and source terms of the same stage; then the first lifts the
+// fluxes and finishes the elements.  For meshes of at most one tile per CU,
+// where each SIMD would hold one wave and a stage is one chain of dependent
+// instructions (FP32 p = 3: 18 thousand cycles of fluxes, then 17 of element
+// work): the shorter of two parallel parts leaves the chain.  Measured at
+// 20,000 elements, us a step with one group of waves / with roles: FP32 p = 1
+// 9.8 / 7.6, p = 2 15.5 / 12.7, p = 3 26.1 / 22.3, FP64 p = 1 11.8 / 9.8, p = 2
+// 20.0 / 17.4.  Two flux groups leave 168 registers, enough for order 1 and
+// FP32 order 2 (FP64 p = 2: 28.7); FP64 order 3 would spill with one group
+// already (81 against 37).  With more tiles than CUs the extra waves cost
+// residency: 51,200 elements, FP32 p = 1, 11.6 against 12.3 to 14.4.
+template <int P, typename Real, int NG>
+__device__ __forceinline__ void step_tile_roles(StepLds<P, Real, true> &T, const StageArgs<Real> &a, const TileView &tv,
+                                                int tile, unsigned e0, int nown, double xh0, double xh1, double dt,
+                                                int *flag)
+{
+    constexpr int K = Ord<P>::K;
+    const MeshView &m = a.m;
+    const int KS = m.KS, stride = m.stride;
+    const int l = (int)threadIdx.x & (BLOCK - 1);
+    const int group = __builtin_amdgcn_readfirstlane((int)threadIdx.x / BLOCK);
+    const bool edges = group != 0;
+    const Buf<Real> bC(a.Cin, 3 * KS, stride), bU(a.Uin, 2 * KS, stride);
+    const double g = a.ph.g;
+    const int *meta = tv.meta + (size_t)tile * BLOCK;
+    const int it0 = l + (group > 1 ? BLOCK : 0);
+    unsigned w0 = ITEM_PAD, w1 = ITEM_PAD, off = 0;
+    int x0 = 0, x1 = 0, lx = 0;
+    Fields<P, Real> s;
+    if (edges) {
+        w0 = tv.items[(size_t)tile * (2 * BLOCK) + it0];
+        if constexpr (NG == 1) w1 = tv.items[(size_t)tile * (2 * BLOCK) + it0 + BLOCK];
+        if (group == NG) T.tri[l] = tv.tri[(size_t)tile * BLOCK + l];
+        if (group == 1 && l < TILE_NV) {
+            const int v = tv.verts[(size_t)tile * TILE_NV + l];
+            if (v >= 0) {
+                const double4 p = m.vtx[(unsigned)v];
+                T.vx[l] = p.x;
+                T.vy[l] = p.y;
+                T.vh[l] = p.z;
+            }
+        }
+        if (w0 != ITEM_PAD && ((w0 >> 20) & 3u) == EK_EXT) x0 = meta[(w0 >> 10) & 255u];
+        if (w1 != ITEM_PAD && ((w1 >> 20) & 3u) == EK_EXT) x1 = meta[(w1 >> 10) & 255u];
+    } else {
+        // a lane past the ring repeats the tile's first element, as in step_tile
+        const int id = l < nown ? (int)e0 + l : meta[l];
+        lx = id >= 0 ? l : 0;
+        off = (id >= 0 ? (unsigned)id : e0) * (unsigned)sizeof(Real);
+        load_state<P, Real>(bC, bU, KS, off, s);
+        sh_copy_state<P, Real, true>(T.S, l, s);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int st = 0; st < 2; ++st) {
+        const bool use0 = w0 != ITEM_PAD && !(st && (w0 & ITEM_RING));
+        const bool use1 = w1 != ITEM_PAD && !(st && (w1 & ITEM_RING));
+        const bool mine = !edges && (st == 0 || l < nown);
+        Acc<P, Real> A;
+        Geo G;
+        double hbh[3];
+        Real cn[3][K];
+        if (edges) {
+            const double xihat = st ? xh1 : xh0;
+            ShItem<P, Real> r0, r1;
+            if (use0) sh_flux<P, Real, true>(T.S, KS, bC, bU, TileSrc<P, Real, true>{T, x0}, w0, xihat, g, r0);
+            if (use0) sh_store<P, Real, true>(T.S, it0, w0, r0);
+            if (use1) sh_flux<P, Real, true>(T.S, KS, bC, bU, TileSrc<P, Real, true>{T, x1}, w1, xihat, g, r1);
+            if (use1) sh_store<P, Real, true>(T.S, it0 + BLOCK, w1, r1);
+        } else if (mine) {
+            tile_geo<P, Real, true>(T, lx, G);
+            hb_modes(G, hbh);
+            acc_init<P, Real>(A, s, true);
+            volume_term<P, Real>(s, hbh, G, g, dt, A);
+            source_term<P, Real>(s, G, a.ph, dt, A);
+            if (st) {
+#pragma unroll
+                for (int j = 0; j < 3; ++j)
+#pragma unroll
+                    for (int q = 0; q < K; ++q) cn[j][q] = bC.ld(j * KS + q, off);
+            }
+        }
+        __syncthreads();
+        if (mine) {
+            sh_lift<P, Real, true>(T.S, G, lx, dt, A);
+            if constexpr (Acc<P, Real>::SPLIT) {
+#pragma unroll
+                for (int q = 0; q < K; ++q) {
+                    A.L[1][q] += Real(A.W[0][q]);
+                    A.L[2][q] += Real(A.W[1][q]);
+                }
+            }
+            if (a.src) {
+                const Buf<Real> bS(a.src, 3 * KS, stride);
+                const Real rdt = Real(dt);
+#pragma unroll
+                for (int j = 0; j < 3; ++j)
+#pragma unroll
+                    for (int q = 0; q < K; ++q) A.L[j][q] = fma(rdt, bS.ld(j * KS + q, off), A.L[j][q]);
+            }
+            if (st) {
+#pragma unroll
+                for (int j = 0; j < 3; ++j)
+#pragma unroll
+                    for (int q = 0; q < K; ++q) A.L[j][q] = Real(0.5) * cn[j][q] + Real(0.5) * A.L[j][q];
+            }
+            solve_u<P, Real>(A.L[0], A.L[1], A.L[2], hbh, K, s.u, s.v);
+            Real chk = 0;
+#pragma unroll
+            for (int q = 0; q < K; ++q) {
+                s.xi[q] = A.L[0][q];
+                s.U[q] = A.L[1][q];
+                s.V[q] = A.L[2][q];
+                chk += s.xi[q] + s.U[q] + s.V[q] + s.u[q] + s.v[q];
+            }
+            const double Hmean = SQRT2 * double(s.xi[0]) + (G.h[0] + G.h[1] + G.h[2]) * (1.0 / 3.0);
+            if (!(Hmean > 0.0) || !isfinite(chk)) flag[0] = 1;
+        }
+        if (st == 0) {
+            if (!edges) sh_copy_state<P, Real, true>(T.S, l, s);
+            __syncthreads();
+        } else if (mine) {
+            (void)store_state<P, Real, CPOL_THROUGH>(a, off, s.xi, s.U, s.V, s.u, s.v);
+        }
+    }
+}
+
+// flux groups of the kernel with roles; 0: not built
+template <int P, typename Real>
+constexpr int flux_groups()
+{
+    return P == 1 || (P == 2 && sizeof(Real) == 4) ? 2 : P == 3 && sizeof(Real) == 8 ? 0 : 1;
+}
+
+template <int P, typename Real, int NG = flux_groups<P, Real>()>
+__global__ void __launch_bounds__((1 + NG) * BLOCK) __attribute__((amdgpu_waves_per_eu(1 + NG, 8)))
+k_step_roles(StageArgs<Real> a, TileView tv, double xihat2)
+{
+    // one block per CU: fluxes beside the state copy
+    __shared__ StepLds<P, Real, true> T;
+    load_trace_lds<P, Real, true>(T.S);
+    double xh0 = a.xihat, xh1 = xihat2, dt = a.dt;
+    if (a.inst) {
+        if (!a.inst->run) return;   // the step's clock stopped (failure); uniform over the block
+        xh0 = a.inst->xh[0];
+        xh1 = a.inst->xh[1];
+        dt = a.inst->dt;
+    }
+    const int tile = xcd_block(blockIdx.x, gridDim.x);
+    const int e0 = tile * tv.len, left = a.m.ne - e0;
+    step_tile_roles<P, Real, NG>(T, a, tv, tile, (unsigned)e0, left < tv.len ? left : tv.len, xh0, xh1, dt, a.flag);
 }
 
 // ---- tile data, one block per tile
@@ -437,22 +599,27 @@ __global__ void __launch_bounds__(BLOCK) k_build_tiles(MeshView m, int ne, TileV
 }  // namespace
 
 template <int P, typename Real>
-hipError_t step_sh_p(const void *args, const TileView &tv, double xihat2, Sink &k)
+hipError_t step_sh_p(const void *args, const TileView &tv, double xihat2, int ncu, Sink &k)
 {
     StageArgs<Real> a = *static_cast<const StageArgs<Real> *>(args);
     TileView t = tv;
     void *kargs[] = {&a, &t, &xihat2};
-    return emit(k, reinterpret_cast<const void *>(&k_step_sh<P, Real>), dim3((a.m.ne + t.len - 1) / t.len), dim3(BLOCK),
-                kargs);
+    const dim3 grid((a.m.ne + t.len - 1) / t.len);
+    constexpr int ng = flux_groups<P, Real>();
+    if constexpr (ng > 0) {
+        if ((int)grid.x <= ncu)
+            return emit(k, reinterpret_cast<const void *>(&k_step_roles<P, Real>), grid, dim3((1 + ng) * BLOCK), kargs);
+    }
+    return emit(k, reinterpret_cast<const void *>(&k_step_sh<P, Real>), grid, dim3(BLOCK), kargs);
 }
 
-hipError_t launch_step_sh(int p, bool fp32, const void *args, const TileView &tv, double xihat2, Sink &k)
+hipError_t launch_step_sh(int p, bool fp32, const void *args, const TileView &tv, double xihat2, int ncu, Sink &k)
 {
     if (tv.len <= 0) return hipErrorInvalidValue;
     switch (p) {
-    case 1: return fp32 ? step_sh_p<1, float>(args, tv, xihat2, k) : step_sh_p<1, double>(args, tv, xihat2, k);
-    case 2: return fp32 ? step_sh_p<2, float>(args, tv, xihat2, k) : step_sh_p<2, double>(args, tv, xihat2, k);
-    case 3: return fp32 ? step_sh_p<3, float>(args, tv, xihat2, k) : step_sh_p<3, double>(args, tv, xihat2, k);
+    case 1: return fp32 ? step_sh_p<1, float>(args, tv, xihat2, ncu, k) : step_sh_p<1, double>(args, tv, xihat2, ncu, k);
+    case 2: return fp32 ? step_sh_p<2, float>(args, tv, xihat2, ncu, k) : step_sh_p<2, double>(args, tv, xihat2, ncu, k);
+    case 3: return fp32 ? step_sh_p<3, float>(args, tv, xihat2, ncu, k) : step_sh_p<3, double>(args, tv, xihat2, ncu, k);
     }
     return hipErrorInvalidValue;
 }
