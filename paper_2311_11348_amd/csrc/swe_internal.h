@@ -230,7 +230,8 @@ hipError_t launch_mass_noalloc(const MeshView &m, bool fp32, const void *C, doub
 hipError_t mass_scratch(double **out);
 int mass_partials(int ne);
 hipError_t launch_batch_stage(int p, bool fp32, int mode, int tile, const BatchArgs &b, int grid, Sink &k);
-hipError_t launch_batch_clock(InstDesc *inst, const int *flags, int n, Sink &k);
+// clocks of the instances of one order (order < 0: of every instance)
+hipError_t launch_batch_clock(InstDesc *inst, const int *flags, int n, int order, Sink &k);
 // write one instance descriptor in stream order (no host buffer outlives the call)
 hipError_t launch_inst_set(InstDesc *inst, const InstDesc &v, hipStream_t s);
 // copy an instance's mesh arrays into a pool, offsetting vertex and element ids

@@ -296,10 +296,10 @@ __device__ __forceinline__ void clock_advance(InstDesc &I, int flag)
     I.steps_left -= 1;
 }
 
-__global__ void __launch_bounds__(BLOCK) k_batch_clock(InstDesc *inst, const int *flags, int n)
+__global__ void __launch_bounds__(BLOCK) k_batch_clock(InstDesc *inst, const int *flags, int n, int order)
 {
     const int i = blockIdx.x * BLOCK + threadIdx.x;
-    if (i >= n) return;
+    if (i >= n || (order >= 0 && inst[i].order != order)) return;
     clock_advance(inst[i], flags[i]);
 }
 
@@ -1665,10 +1665,10 @@ hipError_t launch_place_items(const unsigned *items, const int *item_off, int nb
     return hipGetLastError();
 }
 
-hipError_t launch_batch_clock(InstDesc *inst, const int *flags, int n, Sink &k)
+hipError_t launch_batch_clock(InstDesc *inst, const int *flags, int n, int order, Sink &k)
 {
     if (n <= 0) return hipSuccess;
-    void *kargs[] = {&inst, &flags, &n};
+    void *kargs[] = {&inst, &flags, &n, &order};
     return emit(k, reinterpret_cast<const void *>(&k_batch_clock), dim3((n + BLOCK - 1) / BLOCK), dim3(BLOCK), kargs);
 }
 
