@@ -275,6 +275,8 @@ StageArgs<Real> make_args(const swe_ctx *c)
 struct Lanes {
     swe_ctx *c;
     Sink a, b;           // base work, correction work
+    Sink r;              // graph: the base pass's rest, on a branch of its own
+    bool rest = false;   // it has nodes to join
     bool graph = false, chain = false;
     explicit Lanes(swe_ctx *cc) : c(cc)
     {
@@ -295,6 +297,8 @@ struct Lanes {
         if (graph) {
             b.ndep = a.ndep;
             for (int i = 0; i < Sink::MAXDEP; ++i) b.dep[i] = a.dep[i];
+            r = b;
+            rest = false;
             return hipSuccess;
         }
         const hipError_t e = hipEventRecord(c->ev_ready, c->s_base);
@@ -304,7 +308,7 @@ struct Lanes {
     hipError_t join()
     {
         if (chain) return hipSuccess;
-        if (graph) return a.join(b) ? hipSuccess : hipErrorInvalidValue;
+        if (graph) return a.join(b) && (!rest || a.join(r)) ? hipSuccess : hipErrorInvalidValue;
         const hipError_t e = hipEventRecord(c->ev_corr, c->s_corr);
         return e == hipSuccess ? hipStreamWaitEvent(c->s_base, c->ev_corr, 0) : e;
     }
@@ -398,7 +402,11 @@ hipError_t launch_base(Lanes &L, int mode, StageArgs<Real> &a, int64_t end)
         StageArgs<Real> r = a;
         r.e_off = (int)off;
         r.m.ne = (int)(end - off);
-        e = launch_stage(b, c->fp32, mode, true, &r, L.a);
+        // in a graph with branches the rest is one of its own: it fills a few
+        // dozen blocks for as long as the whole first part takes
+        const bool branch = L.graph && !L.chain && cov > 0;
+        if (branch) L.rest = true;
+        e = launch_stage(b, c->fp32, mode, true, &r, branch ? L.r : L.a);
     }
     return e;
 }
