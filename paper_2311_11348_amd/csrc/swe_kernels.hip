@@ -930,97 +930,113 @@ __global__ void __launch_bounds__(BLOCK) k_indicator(StageArgs<Real> a, double t
                             p_new);
 }
 
-// Apply the new order of element e: drop modes above K(p_new) from every state
-// buffer and re-solve u if the order changed; whether the element is listed
-// (its order or a neighbour's above p_base) goes to *listed.
-template <int PM, typename Real>
-__device__ __forceinline__ int apply_element(const StageArgs<Real> &a, unsigned e, const signed char *p_new,
-                                             signed char *p_cur, int p_base, bool *listed)
+// Whether element e's right-hand side has a correction: its new order or a
+// neighbour's is above p_base.
+__device__ __forceinline__ bool listed_element(const MeshView &m, unsigned e, int pn, const signed char *p_new,
+                                               int p_base)
 {
-    constexpr int K = Ord<PM>::K;
-    const MeshView &m = a.m;
-    const int KS = m.KS, stride = m.stride;
-    const unsigned off = e * (unsigned)sizeof(Real);
-    const int pn = p_new[e];
-    const int po = p_cur[e];
-    const Buf<int> bNb(m.enb, 3, stride);
+    const Buf<int> bNb(m.enb, 3, m.stride);
     bool l = pn > p_base;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         const int nb = bNb.ld(k, e * 4u);
         if (nb >= 0 && p_new[nb] > p_base) l = true;
     }
-    *listed = l;
-    if (pn != po) {
-        const int Kn = KOFP[pn];
-        Buf<Real> b0(a.Cout, 3 * KS, stride), b1(a.Calt, 3 * KS, stride);
-        Buf<Real> u1(a.Ualt, 2 * KS, stride);
-        Real xi[K], U[K], V[K];
+    return l;
+}
+
+// Apply the new order pn of element e: if it differs from the current one,
+// drop modes above K(pn) from every state buffer and re-solve u.
+template <int PM, typename Real>
+__device__ __forceinline__ void apply_element(const StageArgs<Real> &a, unsigned e, int pn, signed char *p_cur)
+{
+    constexpr int K = Ord<PM>::K;
+    const MeshView &m = a.m;
+    const int KS = m.KS, stride = m.stride;
+    const unsigned off = e * (unsigned)sizeof(Real);
+    if (pn == p_cur[e]) return;
+    const int Kn = KOFP[pn];
+    Buf<Real> b0(a.Cout, 3 * KS, stride), b1(a.Calt, 3 * KS, stride);
+    Buf<Real> u1(a.Ualt, 2 * KS, stride);
+    Real xi[K], U[K], V[K];
 #pragma unroll
-        for (int q = 0; q < K; ++q) {
-            const bool keep = q < Kn;
-            xi[q] = keep ? b0.ld(0 * KS + q, off) : Real(0);
-            U[q] = keep ? b0.ld(1 * KS + q, off) : Real(0);
-            V[q] = keep ? b0.ld(2 * KS + q, off) : Real(0);
-            if (!keep) {
+    for (int q = 0; q < K; ++q) {
+        const bool keep = q < Kn;
+        xi[q] = keep ? b0.ld(0 * KS + q, off) : Real(0);
+        U[q] = keep ? b0.ld(1 * KS + q, off) : Real(0);
+        V[q] = keep ? b0.ld(2 * KS + q, off) : Real(0);
+        if (!keep) {
 #pragma unroll
-                for (int j = 0; j < 3; ++j) { b0.st(j * KS + q, off, Real(0)); b1.st(j * KS + q, off, Real(0)); }
-                u1.st(0 * KS + q, off, Real(0));
-                u1.st(1 * KS + q, off, Real(0));
-            }
+            for (int j = 0; j < 3; ++j) { b0.st(j * KS + q, off, Real(0)); b1.st(j * KS + q, off, Real(0)); }
+            u1.st(0 * KS + q, off, Real(0));
+            u1.st(1 * KS + q, off, Real(0));
         }
-        Geo G;
-#pragma unroll
-        for (int v = 0; v < 3; ++v) G.h[v] = m.vtx[(unsigned)Buf<int>(m.ev, 3, stride).ld(v, e * 4u)].z;
-        double hbh[3];
-        hb_modes(G, hbh);
-        Real u[K], v[K];
-        solve_u<PM, Real>(xi, U, V, hbh, Kn, u, v);
-        Buf<Real> bu(a.Uout, 2 * KS, stride);
-#pragma unroll
-        for (int q = 0; q < K; ++q) {
-            bu.st(0 * KS + q, off, u[q]);
-            bu.st(1 * KS + q, off, v[q]);
-        }
-        p_cur[e] = (signed char)pn;
     }
-    return pn;
+    Geo G;
+#pragma unroll
+    for (int v = 0; v < 3; ++v) G.h[v] = m.vtx[(unsigned)Buf<int>(m.ev, 3, stride).ld(v, e * 4u)].z;
+    double hbh[3];
+    hb_modes(G, hbh);
+    Real u[K], v[K];
+    solve_u<PM, Real>(xi, U, V, hbh, Kn, u, v);
+    Buf<Real> bu(a.Uout, 2 * KS, stride);
+#pragma unroll
+    for (int q = 0; q < K; ++q) {
+        bu.st(0 * KS + q, off, u[q]);
+        bu.st(1 * KS + q, off, v[q]);
+    }
+    p_cur[e] = (signed char)pn;
 }
 
 // Apply the new orders of a context's elements, flag elements that need a
-// correction and append them to the list of their order (one atomic per
-// wave and order).
+// correction and append them to the list of their order.  The lists come
+// first, so that their atomics are under way while the few elements whose
+// order changed are solved again, and a block takes its places in every list
+// with one atomic each: with one per wave, some 2,000 to 6,000 atomics on one
+// cache line held up a 131,072-element update (APPLYBEFORE -> APPLYNOW us).
 template <int PM, typename Real>
 __global__ void __launch_bounds__(BLOCK) k_apply_order(StageArgs<Real> a, const signed char *p_new,
                                                        signed char *p_cur, int p_base, int lcap, InstDesc *clock,
                                                        const int *flag)
 {
+    __shared__ int cnt[4][BLOCK / 64];   // listed elements of an order in each wave, then where they go
     const unsigned e = blockIdx.x * BLOCK + threadIdx.x;
     // a step graph's clock (no other thread of this kernel reads the instance)
     if (clock && e == 0) clock_advance(*clock, flag[0]);
     const bool live = e < (unsigned)a.m.ne;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int pn = 0;
     bool listed = false;
     if (live) {
-        pn = apply_element<PM, Real>(a, e, p_new, p_cur, p_base, &listed);
+        pn = p_new[e];
+        listed = listed_element(a.m, e, pn, p_new, p_base);
         a.inlist[e] = listed ? 1 : 0;
     }
-    // wave-aggregated append to the list of order pn
-    const int lane = threadIdx.x & 63;
+    int rank = 0;
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
-        const bool mine = live && listed && pn == p;
+        const bool mine = listed && pn == p;
         const unsigned long long mask = __ballot(mine);
-        if (mask == 0ull) continue;
-        const int leader = __ffsll((long long)mask) - 1;
-        int base = 0;
-        if (lane == leader) base = atomicAdd(&a.cntw[p], __popcll(mask));
-        base = __shfl(base, leader);
-        if (mine) {
-            // base + rank < lcap: each element is appended at most once per update
-            const int rank = __popcll(mask & ((1ull << lane) - 1ull));
-            if (base + rank < lcap) a.listw[(size_t)p * (size_t)lcap + (size_t)(base + rank)] = (int)e;
+        if (mine) rank = __popcll(mask & ((1ull << lane) - 1ull));
+        if (lane == 0) cnt[p][wave] = __popcll(mask);
+    }
+    __syncthreads();
+    if (threadIdx.x < 4) {
+        int n = 0;
+        for (int w = 0; w < BLOCK / 64; ++w) n += cnt[threadIdx.x][w];
+        int base = n ? atomicAdd(&a.cntw[threadIdx.x], n) : 0;
+        for (int w = 0; w < BLOCK / 64; ++w) {
+            const int k = cnt[threadIdx.x][w];
+            cnt[threadIdx.x][w] = base;
+            base += k;
         }
+    }
+    if (live) apply_element<PM, Real>(a, e, pn, p_cur);
+    __syncthreads();
+    if (listed) {
+        // at < lcap: each element is appended at most once per update
+        const int at = cnt[pn][wave] + rank;
+        if (at < lcap) a.listw[(size_t)pn * (size_t)lcap + (size_t)at] = (int)e;
     }
 }
 
@@ -1076,8 +1092,7 @@ __global__ void __launch_bounds__(BLOCK) k_batch_apply(BatchArgs b)
     a.Calt = static_cast<Real *>(b.pool.C1);
     a.Uout = static_cast<Real *>(b.pool.U0);
     a.Ualt = static_cast<Real *>(b.pool.U1);
-    bool listed = false;
-    (void)apply_element<PM, Real>(a, e, b.pool.pnew, b.pool.ep, I.p_lo, &listed);
+    apply_element<PM, Real>(a, e, b.pool.pnew[e], b.pool.ep);
 }
 
 // ------------------------------------------------------------ minimum depth control
