@@ -265,13 +265,25 @@ StageArgs<Real> make_args(const swe_ctx *c)
     return a;
 }
 
+// Whether a step graph is one chain (the list kernels after the base pass of
+// the same stage) instead of branches.  Orders re-chosen on the device: their
+// lists are short, and a fork and a join cost more than the list kernel's own
+// time (measured on the adaptive tsunami).  A separated step on a static map
+// of a small mesh: in the chain the correction kernel finishes its elements
+// itself, so fork, join and epilogue go (us a step with branches / as a chain,
+// dam break p1-2: 7,200 elements FP64 61.5 / 52.6, FP32 60.1 / 45.3; 259,200
+// FP64 127.7 / 119.8; 352,800 FP32 110.8 / 101.8, FP64 170.5 / 184.7; 720,000
+// FP32 166 / 177); on larger ones the branches overlap long lists with the
+// base pass.
+bool one_chain(const swe_ctx *c)
+{
+    if (c->cfg.adapt) return true;
+    return c->cfg.separate == 1 && (c->ne + BLOCK - 1) / BLOCK <= (int64_t)c->ncu * (c->fp32 ? 6 : 4);
+}
+
 // Where the kernels of a step go: the context's two streams joined by
-// events, or two branches of a step graph under construction (graph set).
-// A step graph whose orders are re-chosen on the device is one chain (the
-// list kernels after the base pass of the same stage): its lists are short,
-// and a fork and a join cost more than the list kernel's own time (measured
-// on the adaptive tsunami; the static maps of the dam break keep the two
-// branches, where they overlap long lists with the base pass).
+// events, or the branches (or the chain) of a step graph under construction
+// (graph set).
 struct Lanes {
     swe_ctx *c;
     Sink a, b;           // base work, correction work
@@ -283,7 +295,7 @@ struct Lanes {
         a.s = c->s_base;
         b.s = c->s_corr;
     }
-    Lanes(swe_ctx *cc, hipGraph_t g) : c(cc), graph(true), chain(cc->cfg.adapt != 0)
+    Lanes(swe_ctx *cc, hipGraph_t g) : c(cc), graph(true), chain(one_chain(cc))
     {
         a.g = g;
         b.g = g;
@@ -574,6 +586,20 @@ hipError_t enqueue_separated_hetero(Lanes &L, int mode, int in, int out, double 
     return launch_epi_all(b, pm, c->fp32, mode, &a, list_blocks(c), (int)c->ne, L.a);
 }
 
+// One launch per order-partitioned stage in a step graph, on meshes whose
+// base blocks (the elements [0, end)) need few rounds at the list kernel's
+// registers: one block per CU in FP64, two or more in FP32.  Measured, us a
+// step with separate launches / with one: FP64 adaptive orders 1-3, 74 blocks
+// 63.8 / 45.2, 378 blocks 73.7 / 60.4, 512 blocks 72.0 / 77.5; static p1-2,
+// 25 blocks 42.3 / 20.1, 394 blocks 58.7 / 53.5, 700 blocks 76.3 / 82.3; FP32
+// static p1-2, 50 blocks 40.4 / 17.4, 1,200 blocks 87.5 / 76.6, adaptive 1,378
+// blocks 76.3 / 72.0, 2,813 blocks 110 / 127.
+bool one_launch_partitioned(const swe_ctx *c, int64_t end)
+{
+    if (c->cfg.p_base < 1 || (c->fp32 && c->cfg.p_max == 3)) return false;
+    return 4 * ((end + BLOCK - 1) / BLOCK) <= (int64_t)c->ncu * (c->fp32 ? 24 : 7);
+}
+
 // Order-partitioned stage: the base kernel does every element of order
 // p_base whose neighbours are all of order p_base (branch A); each order's
 // listed elements get their full stage from a kernel of that order, all on
@@ -593,11 +619,19 @@ hipError_t enqueue_partitioned(Lanes &L, int mode, int in, int out, double tstag
     L.time(a, mode == MODE_STAGE2 ? 1 : 0, tstage, dt);
     a.inlist = c->d_inlist;
     a.skip_listed = 1;
+    const int64_t end = c->grouped ? c->n_unlisted : c->ne;
+    if (L.graph && one_launch_partitioned(c, end)) {
+        a.list = c->d_list;
+        a.count = c->d_cnt;
+        const int64_t nsh = c->d_items ? std::min(c->item_blocks, (end + BLOCK - 1) / BLOCK) : 0;
+        return launch_part_all(b, pm, c->fp32, mode, &a, list_blocks(c), (int)c->ne, (int)nsh, (int)end, c->d_items,
+                               c->d_item_off, L.a);
+    }
     hipError_t e = L.fork();
     if (e != hipSuccess) return e;
     // with the elements grouped (static order map) the unlisted ones are the
     // first n_unlisted: the base pass covers them only
-    e = launch_base<Real>(L, mode, a, c->grouped ? c->n_unlisted : c->ne);
+    e = launch_base<Real>(L, mode, a, end);
     if (e != hipSuccess) return e;
     // the listed elements of every order in one launch on branch B
     a.skip_listed = 0;

@@ -188,6 +188,11 @@ hipError_t launch_build_tiles(const MeshView &m, int ne, const TileView &tv, int
 // full stage (order-partitioned scheme), correction and epilogue (order-
 // separated scheme, lo = b)
 hipError_t launch_full_all(int lo, int pn, bool fp32, int mode, const void *args, int nblk, int lcap, Sink &k);
+// a whole order-partitioned stage in one launch (args as for both kernels; base
+// order b >= 1, its pass over the elements [0, e_end), the first nsh blocks of
+// them with edge items; not for FP32 with pn = 3)
+hipError_t launch_part_all(int b, int pn, bool fp32, int mode, const void *args, int nblk, int lcap, int nsh, int e_end,
+                           const unsigned *items, const int *item_off, Sink &k);
 hipError_t launch_corr_all(int b, int pn, bool fp32, const void *args, double dt, int nblk, int lcap, Sink &k);
 hipError_t launch_epi_all(int b, int pn, bool fp32, int mode, const void *args, int nblk, int lcap, Sink &k);
 // The correction of the order-separated scheme for the listed elements
