@@ -238,7 +238,7 @@ class Context:
         self._check(self.L.swe_sync(self.h))
 
     def state(self):
-        c = np.zeros((self.ne, 3, self.K))
+        c = np.empty((self.ne, 3, self.K))   # written in full
         t = C.c_double()
         self._check(self.L.swe_get_state(self.h, _d(c), C.byref(t)))
         return c, t.value

@@ -58,3 +58,33 @@ def test_state_round_trip(p, ne, precision):
         r1 = ctx.rhs(0.0, np.zeros_like(c0))
         assert np.all(np.abs((r0 - r1) - ref) <= 4 * tol * (np.abs(ref) + np.abs(r1)) + 1e-300)
         assert np.array_equal(ctx.state()[0], got)
+
+
+@pytest.mark.parametrize("precision,p,n", [(swe.SWE_FP32_WB, 2, 70), (swe.SWE_FP64, 1, 200), (swe.SWE_FP64, 3, 141)])
+def test_large_read_back_threads(precision, p, n):
+    """Read-backs of a few parts of the pinned ring, by two threads on two
+    contexts at once: the bytes of a read alone (the round trip's tolerance
+    against what was set)."""
+    import threading
+    prob = I.config_c3(n=n)
+    prob.p[:], prob.p_base, prob.p_max, prob.adapt = p, p, p, 0
+    c0 = I.random_state(prob.mesh, prob.p, p, 9, prob.hb_vertex)
+    tol = 2.0 ** -51 if precision == swe.SWE_FP64 else 2.0 ** -23
+    with swe.context_for(prob, precision=precision) as a, swe.context_for(prob, precision=precision) as b:
+        a.set_state(c0)
+        b.set_state(2.0 * c0)
+        alone, alone2 = a.state()[0], b.state()[0]
+        assert np.all(np.abs(alone - c0) <= tol * np.abs(c0))
+        assert np.array_equal(alone2, 2.0 * alone)
+        bad = []
+
+        def read(ctx, ref):
+            for _ in range(4):
+                if not np.array_equal(ctx.state()[0], ref):
+                    bad.append(ctx)
+        th = [threading.Thread(target=read, args=x) for x in ((a, alone), (b, alone2))]
+        for t in th:
+            t.start()
+        for t in th:
+            t.join()
+        assert not bad
