@@ -240,141 +240,155 @@ k_step_sh(StageArgs<Real> a, TileView tv, double xihat2)
 // fluxes and finishes the elements.  For meshes of at most one tile per CU,
 // where each SIMD would hold one wave and a stage is one chain of dependent
 // instructions (FP32 p = 3: 18 thousand cycles of fluxes, then 17 of element
-// work): the shorter of two parallel parts leaves the chain.  Measured at
-// 20,000 elements, us a step with one group of waves / with roles: FP32 p = 1
-// 9.8 / 7.6, p = 2 15.5 / 12.7, p = 3 26.1 / 22.3, FP64 p = 1 11.8 / 9.8, p = 2
-// 20.0 / 17.4.  Two flux groups leave 168 registers, enough for order 1 and
-// FP32 order 2 (FP64 p = 2: 28.7); FP64 order 3 would spill with one group
-// already (81 against 37).  With more tiles than CUs the extra waves cost
-// residency: 51,200 elements, FP32 p = 1, 11.6 against 12.3 to 14.4.
+// work): the shorter of two parallel parts leaves the chain.  The roles are
+// separate code from the first load to the last store, so that neither holds
+// the other's registers (joined between the barriers, FP32 p = 2 took 205
+// instead of 130).  Measured at 20,000 elements, us a step with one group of
+// waves / with roles: FP32 p = 1 10.3 / 7.7, p = 2 15.9 / 11.7, p = 3 25.8 /
+// 20.1, FP64 p = 1 12.1 / 9.5, p = 2 20.3 / 17.4 (with two flux groups 18.3);
+// FP64 p = 3 spills with one flux group already (36.7 / 53).  With more tiles
+// than CUs the extra waves cost residency (51,200 elements, FP32 p = 2: 19.5 /
+// 21.3); order 1 fits two blocks of two groups on a CU (65,522 elements, FP32
+// 12.1 / 11.0, FP64 16.4 / 14.8; 96,800: FP32 14.5 / 16.9).
+// A block barrier that waves with different roles reach at different places
+// of the code: every wave of the block meets the same number of them, in the
+// same order (the role is uniform over a wave, and the hardware counts waves).
+__device__ __forceinline__ void role_barrier() { __syncthreads(); }
+
+// The edge waves of a tile: group 1..NG of the block's groups of four.
 template <int P, typename Real, int NG>
-__device__ __forceinline__ void step_tile_roles(StepLds<P, Real, true> &T, const StageArgs<Real> &a, const TileView &tv,
-                                                int tile, unsigned e0, int nown, double xh0, double xh1, double dt,
-                                                int *flag)
+__device__ __forceinline__ void tile_edges(StepLds<P, Real, true> &T, const StageArgs<Real> &a,
+                                           const TileView &tv, int tile, int group, double xh0, double xh1)
+{
+    const MeshView &m = a.m;
+    const int KS = m.KS, l = (int)threadIdx.x & (BLOCK - 1), it0 = l + (group > 1 ? BLOCK : 0);
+    const Buf<Real> bC(a.Cin, 3 * KS, m.stride), bU(a.Uin, 2 * KS, m.stride);
+    const double g = a.ph.g;
+    const int *meta = tv.meta + (size_t)tile * BLOCK;
+    const unsigned w0 = tv.items[(size_t)tile * (2 * BLOCK) + it0];
+    const unsigned w1 = NG == 1 ? tv.items[(size_t)tile * (2 * BLOCK) + it0 + BLOCK] : ITEM_PAD;
+    if (group == NG) T.tri[l] = tv.tri[(size_t)tile * BLOCK + l];
+    if (group == 1 && l < TILE_NV) {
+        const int v = tv.verts[(size_t)tile * TILE_NV + l];
+        if (v >= 0) {
+            const double4 p = m.vtx[(unsigned)v];
+            T.vx[l] = p.x;
+            T.vy[l] = p.y;
+            T.vh[l] = p.z;
+        }
+    }
+    int x0 = 0, x1 = 0;
+    if (w0 != ITEM_PAD && ((w0 >> 20) & 3u) == EK_EXT) x0 = meta[(w0 >> 10) & 255u];
+    if (w1 != ITEM_PAD && ((w1 >> 20) & 3u) == EK_EXT) x1 = meta[(w1 >> 10) & 255u];
+    role_barrier();
+#pragma unroll
+    for (int st = 0; st < 2; ++st) {
+        const double xihat = st ? xh1 : xh0;
+        const bool use0 = w0 != ITEM_PAD && !(st && (w0 & ITEM_RING));
+        const bool use1 = w1 != ITEM_PAD && !(st && (w1 & ITEM_RING));
+        ShItem<P, Real> r;
+        if (use0) {
+            sh_flux<P, Real, true>(T.S, KS, bC, bU, TileSrc<P, Real, true>{T, x0}, w0, xihat, g, r);
+            sh_store<P, Real, true>(T.S, it0, w0, r);
+        }
+        if (use1) {
+            sh_flux<P, Real, true>(T.S, KS, bC, bU, TileSrc<P, Real, true>{T, x1}, w1, xihat, g, r);
+            sh_store<P, Real, true>(T.S, it0 + BLOCK, w1, r);
+        }
+        role_barrier();                     // the fluxes are in place, the state copies read
+        if (st == 0) role_barrier();        // the first stage's state is in place
+    }
+}
+
+// The element waves of a tile.
+template <int P, typename Real>
+__device__ __forceinline__ void tile_elements(StepLds<P, Real, true> &T, const StageArgs<Real> &a,
+                                              const TileView &tv, int tile, unsigned e0, int nown, double dt, int *flag)
 {
     constexpr int K = Ord<P>::K;
     const MeshView &m = a.m;
-    const int KS = m.KS, stride = m.stride;
-    const int l = (int)threadIdx.x & (BLOCK - 1);
-    const int group = __builtin_amdgcn_readfirstlane((int)threadIdx.x / BLOCK);
-    const bool edges = group != 0;
+    const int KS = m.KS, stride = m.stride, l = (int)threadIdx.x & (BLOCK - 1);
     const Buf<Real> bC(a.Cin, 3 * KS, stride), bU(a.Uin, 2 * KS, stride);
     const double g = a.ph.g;
-    const int *meta = tv.meta + (size_t)tile * BLOCK;
-    const int it0 = l + (group > 1 ? BLOCK : 0);
-    unsigned w0 = ITEM_PAD, w1 = ITEM_PAD, off = 0;
-    int x0 = 0, x1 = 0, lx = 0;
+    // a lane past the ring repeats the tile's first element, as in step_tile
+    const int id = l < nown ? (int)e0 + l : tv.meta[(size_t)tile * BLOCK + l];
+    const int lx = id >= 0 ? l : 0;
+    const unsigned off = (id >= 0 ? (unsigned)id : e0) * (unsigned)sizeof(Real);
     Fields<P, Real> s;
-    if (edges) {
-        w0 = tv.items[(size_t)tile * (2 * BLOCK) + it0];
-        if constexpr (NG == 1) w1 = tv.items[(size_t)tile * (2 * BLOCK) + it0 + BLOCK];
-        if (group == NG) T.tri[l] = tv.tri[(size_t)tile * BLOCK + l];
-        if (group == 1 && l < TILE_NV) {
-            const int v = tv.verts[(size_t)tile * TILE_NV + l];
-            if (v >= 0) {
-                const double4 p = m.vtx[(unsigned)v];
-                T.vx[l] = p.x;
-                T.vy[l] = p.y;
-                T.vh[l] = p.z;
-            }
-        }
-        if (w0 != ITEM_PAD && ((w0 >> 20) & 3u) == EK_EXT) x0 = meta[(w0 >> 10) & 255u];
-        if (w1 != ITEM_PAD && ((w1 >> 20) & 3u) == EK_EXT) x1 = meta[(w1 >> 10) & 255u];
-    } else {
-        // a lane past the ring repeats the tile's first element, as in step_tile
-        const int id = l < nown ? (int)e0 + l : meta[l];
-        lx = id >= 0 ? l : 0;
-        off = (id >= 0 ? (unsigned)id : e0) * (unsigned)sizeof(Real);
-        load_state<P, Real>(bC, bU, KS, off, s);
-        sh_copy_state<P, Real, true>(T.S, l, s);
-    }
-    __syncthreads();
+    load_state<P, Real>(bC, bU, KS, off, s);
+    sh_copy_state<P, Real, true>(T.S, l, s);
+    role_barrier();
 #pragma unroll
     for (int st = 0; st < 2; ++st) {
-        const bool use0 = w0 != ITEM_PAD && !(st && (w0 & ITEM_RING));
-        const bool use1 = w1 != ITEM_PAD && !(st && (w1 & ITEM_RING));
-        const bool mine = !edges && (st == 0 || l < nown);
-        Acc<P, Real> A;
         Geo G;
+        tile_geo<P, Real, true>(T, lx, G);
         double hbh[3];
-        Real cn[3][K];
-        if (edges) {
-            const double xihat = st ? xh1 : xh0;
-            ShItem<P, Real> r0, r1;
-            if (use0) sh_flux<P, Real, true>(T.S, KS, bC, bU, TileSrc<P, Real, true>{T, x0}, w0, xihat, g, r0);
-            if (use0) sh_store<P, Real, true>(T.S, it0, w0, r0);
-            if (use1) sh_flux<P, Real, true>(T.S, KS, bC, bU, TileSrc<P, Real, true>{T, x1}, w1, xihat, g, r1);
-            if (use1) sh_store<P, Real, true>(T.S, it0 + BLOCK, w1, r1);
-        } else if (mine) {
-            tile_geo<P, Real, true>(T, lx, G);
-            hb_modes(G, hbh);
-            acc_init<P, Real>(A, s, true);
-            volume_term<P, Real>(s, hbh, G, g, dt, A);
-            source_term<P, Real>(s, G, a.ph, dt, A);
-            if (st) {
+        hb_modes(G, hbh);
+        Acc<P, Real> A;
+        Real cn[3][K];   // c^n for the second stage, under way while the edges are lifted
+        acc_init<P, Real>(A, s, true);
+        volume_term<P, Real>(s, hbh, G, g, dt, A);
+        source_term<P, Real>(s, G, a.ph, dt, A);
+        if (st) {
 #pragma unroll
-                for (int j = 0; j < 3; ++j)
+            for (int j = 0; j < 3; ++j)
 #pragma unroll
-                    for (int q = 0; q < K; ++q) cn[j][q] = bC.ld(j * KS + q, off);
-            }
+                for (int q = 0; q < K; ++q) cn[j][q] = bC.ld(j * KS + q, off);
         }
-        __syncthreads();
-        if (mine) {
-            sh_lift<P, Real, true>(T.S, G, lx, dt, A);
-            if constexpr (Acc<P, Real>::SPLIT) {
-#pragma unroll
-                for (int q = 0; q < K; ++q) {
-                    A.L[1][q] += Real(A.W[0][q]);
-                    A.L[2][q] += Real(A.W[1][q]);
-                }
-            }
-            if (a.src) {
-                const Buf<Real> bS(a.src, 3 * KS, stride);
-                const Real rdt = Real(dt);
-#pragma unroll
-                for (int j = 0; j < 3; ++j)
-#pragma unroll
-                    for (int q = 0; q < K; ++q) A.L[j][q] = fma(rdt, bS.ld(j * KS + q, off), A.L[j][q]);
-            }
-            if (st) {
-#pragma unroll
-                for (int j = 0; j < 3; ++j)
-#pragma unroll
-                    for (int q = 0; q < K; ++q) A.L[j][q] = Real(0.5) * cn[j][q] + Real(0.5) * A.L[j][q];
-            }
-            solve_u<P, Real>(A.L[0], A.L[1], A.L[2], hbh, K, s.u, s.v);
-            Real chk = 0;
+        role_barrier();                     // the fluxes are in place
+        if (st && l >= nown) return;         // (no barrier follows)
+        sh_lift<P, Real, true>(T.S, G, lx, dt, A);
+        if constexpr (Acc<P, Real>::SPLIT) {
 #pragma unroll
             for (int q = 0; q < K; ++q) {
-                s.xi[q] = A.L[0][q];
-                s.U[q] = A.L[1][q];
-                s.V[q] = A.L[2][q];
-                chk += s.xi[q] + s.U[q] + s.V[q] + s.u[q] + s.v[q];
+                A.L[1][q] += Real(A.W[0][q]);
+                A.L[2][q] += Real(A.W[1][q]);
             }
-            const double Hmean = SQRT2 * double(s.xi[0]) + (G.h[0] + G.h[1] + G.h[2]) * (1.0 / 3.0);
-            if (!(Hmean > 0.0) || !isfinite(chk)) flag[0] = 1;
         }
+        if (a.src) {
+            const Buf<Real> bS(a.src, 3 * KS, stride);
+            const Real rdt = Real(dt);
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+#pragma unroll
+                for (int q = 0; q < K; ++q) A.L[j][q] = fma(rdt, bS.ld(j * KS + q, off), A.L[j][q]);
+        }
+        if (st) {
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+#pragma unroll
+                for (int q = 0; q < K; ++q) A.L[j][q] = Real(0.5) * cn[j][q] + Real(0.5) * A.L[j][q];
+        }
+        solve_u<P, Real>(A.L[0], A.L[1], A.L[2], hbh, K, s.u, s.v);
+        Real chk = 0;
+#pragma unroll
+        for (int q = 0; q < K; ++q) {
+            s.xi[q] = A.L[0][q];
+            s.U[q] = A.L[1][q];
+            s.V[q] = A.L[2][q];
+            chk += s.xi[q] + s.U[q] + s.V[q] + s.u[q] + s.v[q];
+        }
+        const double Hmean = SQRT2 * double(s.xi[0]) + (G.h[0] + G.h[1] + G.h[2]) * (1.0 / 3.0);
+        if (!(Hmean > 0.0) || !isfinite(chk)) flag[0] = 1;
         if (st == 0) {
-            if (!edges) sh_copy_state<P, Real, true>(T.S, l, s);
-            __syncthreads();
-        } else if (mine) {
-            (void)store_state<P, Real, CPOL_THROUGH>(a, off, s.xi, s.U, s.V, s.u, s.v);
+            sh_copy_state<P, Real, true>(T.S, l, s);
+            role_barrier();
         }
     }
+    (void)store_state<P, Real, CPOL_THROUGH>(a, off, s.xi, s.U, s.V, s.u, s.v);
 }
 
-// flux groups of the kernel with roles; 0: not built
+// flux groups of the kernel with roles for at most one tile per CU; 0: not built
 template <int P, typename Real>
 constexpr int flux_groups()
 {
-    return P == 1 || (P == 2 && sizeof(Real) == 4) ? 2 : P == 3 && sizeof(Real) == 8 ? 0 : 1;
+    return sizeof(Real) == 4 || P == 1 ? 2 : P == 2 ? 1 : 0;
 }
 
-template <int P, typename Real, int NG = flux_groups<P, Real>()>
+template <int P, typename Real, int NG>
 __global__ void __launch_bounds__((1 + NG) * BLOCK) __attribute__((amdgpu_waves_per_eu(1 + NG, 8)))
 k_step_roles(StageArgs<Real> a, TileView tv, double xihat2)
 {
-    // one block per CU: fluxes beside the state copy
     __shared__ StepLds<P, Real, true> T;
     load_trace_lds<P, Real, true>(T.S);
     double xh0 = a.xihat, xh1 = xihat2, dt = a.dt;
@@ -386,7 +400,11 @@ k_step_roles(StageArgs<Real> a, TileView tv, double xihat2)
     }
     const int tile = xcd_block(blockIdx.x, gridDim.x);
     const int e0 = tile * tv.len, left = a.m.ne - e0;
-    step_tile_roles<P, Real, NG>(T, a, tv, tile, (unsigned)e0, left < tv.len ? left : tv.len, xh0, xh1, dt, a.flag);
+    const int group = __builtin_amdgcn_readfirstlane((int)threadIdx.x / BLOCK);
+    if (group)
+        tile_edges<P, Real, NG>(T, a, tv, tile, group, xh0, xh1);
+    else
+        tile_elements<P, Real>(T, a, tv, tile, (unsigned)e0, left < tv.len ? left : tv.len, dt, a.flag);
 }
 
 // ---- tile data, one block per tile
@@ -608,7 +626,13 @@ hipError_t step_sh_p(const void *args, const TileView &tv, double xihat2, int nc
     constexpr int ng = flux_groups<P, Real>();
     if constexpr (ng > 0) {
         if ((int)grid.x <= ncu)
-            return emit(k, reinterpret_cast<const void *>(&k_step_roles<P, Real>), grid, dim3((1 + ng) * BLOCK), kargs);
+            return emit(k, reinterpret_cast<const void *>(&k_step_roles<P, Real, ng>), grid, dim3((1 + ng) * BLOCK),
+                        kargs);
+    }
+    // order 1: two blocks of one flux group each share a CU
+    if constexpr (P == 1) {
+        if ((int)grid.x <= 2 * ncu)
+            return emit(k, reinterpret_cast<const void *>(&k_step_roles<P, Real, 1>), grid, dim3(2 * BLOCK), kargs);
     }
     return emit(k, reinterpret_cast<const void *>(&k_step_sh<P, Real>), grid, dim3(BLOCK), kargs);
 }

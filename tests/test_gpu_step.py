@@ -45,7 +45,7 @@ def test_strip_bitwise(ne, p, precision):
 
 @pytest.mark.parametrize("precision", [swe.SWE_FP64, swe.SWE_FP32_WB])
 @pytest.mark.parametrize("p", [1, 2, 3])
-@pytest.mark.parametrize("n,steps", [(9, 2), (13, 5), (45, 3), (170, 3)])   # 170: more tiles than CUs
+@pytest.mark.parametrize("n,steps", [(9, 2), (13, 5), (45, 3), (170, 3), (235, 2)])   # 256 tiles < 170 < 512 < 235
 def test_open_sea_bitwise(n, steps, p, precision):
     prob = I.config_c2(n=n, p=p, seed=n)
     c0, dt, (a, b) = both(prob, precision, steps, source=n == 13)
