@@ -1048,12 +1048,19 @@ bool one_launch_pays(const swe_ctx *c, int len)
 // in the fourth), or fewer, by eights, where some tile of the mesh is beyond a
 // block (a ring above 64 elements, many boundary edges); below 128 owned
 // elements the ring costs as much as they do, and the mesh keeps two launches
-// per step.
+// per step.  A mesh that leaves CUs without a tile is cut finer, down to 96
+// elements: the tiles' edge items then take one round of the edge waves
+// instead of two, and fewer waves share a SIMD (us a step with 192 / 96
+// elements, 22,050 elements: FP64 p = 1 9.2 / 8.4, p = 2 17.1 / 14.8, p = 3 36.3
+// / 31.3, FP32 p = 2 11.3 / 10.2, p = 3 19.7 / 18.1; 64 elements gain nothing
+// more, and their outside neighbours outnumber them).
 swe_status build_tiles(swe_ctx *c)
 {
     free_tiles(c);
     if (separated(c) || c->cfg.adapt || c->cfg.h_min > 0.0 || !stage_sh_supported(c->cfg.p_max, c->fp32)) return SWE_OK;
-    for (int len = 192; len >= 128 && one_launch_pays(c, len);) {
+    const int64_t fill = (c->ne + c->ncu - 1) / c->ncu;   // elements per CU
+    const int start = fill >= 192 ? 192 : std::max(96, (int)(fill + 7) / 8 * 8), least = fill > 192 ? 128 : 64;
+    for (int len = start; len >= least && one_launch_pays(c, len);) {
         const size_t nt = (size_t)((c->ne + len - 1) / len);
         HIP_TRY(c, hipMalloc(&c->d_tiles, nt * TILE_BYTES));
         TileView t{};
@@ -1292,13 +1299,15 @@ int64_t kept_bytes(int64_t ne, int64_t nv)
 
 // Device bytes of a context's state: C0, C1, U0, U1, the right-hand-side
 // scratch, the shared-flux kernel's edge items (at most 3 per element) and the
-// tiles of the one-launch step (at least 128 elements each).
+// tiles of the one-launch step (at least 128 elements each, 64 on meshes that
+// do not fill the CUs).
 int64_t state_bytes(int64_t ne, int p, bool fp32)
 {
     const int64_t S = (ne + BLOCK - 1) / BLOCK * BLOCK;
     const int64_t K = K_OF[p], w = fp32 ? 4 : 8;
     int64_t b = (2 * 3 * K + 2 * 2 * K + 3 * K) * S * w;
-    if (stage_sh_supported(p, fp32)) b += 3 * 4 * S + 4 * (S / BLOCK + 1) + (int64_t)TILE_BYTES * ((S + 127) / 128);
+    if (stage_sh_supported(p, fp32))
+        b += 3 * 4 * S + 4 * (S / BLOCK + 1) + (int64_t)TILE_BYTES * (S / (S <= 65536 ? 64 : 128) + 1);
     return b;
 }
 
