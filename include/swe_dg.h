@@ -79,10 +79,12 @@ typedef struct {
                                not available with SWE_FP32_WB and p_max = 3 (SWE_EINVAL) */
     void *stream_base;      /* hipStream_t for the base work, or NULL for a library-owned stream */
     void *stream_corr;      /* hipStream_t for the correction work, or NULL */
-    int step_graph;         /* how swe_step enqueues a step: 1 (default) one replayed HIP
-                               graph per step (forcing clock on the device) for separated and
-                               partitioned steps, plain launches for a fused step; 2 always
-                               the graph; 0 always kernel-by-kernel launches */
+    int step_graph;         /* how swe_step enqueues steps: 1 (default) replayed HIP graphs
+                               of one or eight steps (forcing clock on the device) for
+                               separated and partitioned steps, plain launches for a fused
+                               step (one per step for a uniform order of at least 1 without
+                               a minimum depth control where that is the faster, else one per
+                               stage); 2 always the graph; 0 always kernel-by-kernel launches */
     int hetero;             /* 1: heterogeneous stages (the paper's CPU + GPU co-execution,
                                Sec. "Performance results"): with separate = 1 and a static
                                order map, the GPU runs the base pass over every element while
@@ -166,9 +168,10 @@ swe_status swe_set_source(swe_ctx *ctx, const double *coef);
 /* Advance nsteps SSP-RK2 steps of size dt (s).  Work is enqueued on the
  * context's streams; errors detected on the device surface at swe_sync.
  * With a step graph (see step_graph; at most 4 forcing constituents), one
- * step is a graph of kernel nodes (base and correction branches joined
- * where the scheme joins them) replayed nsteps times; stage times and the
- * open-sea elevation are computed on the device from t0 + k dt. */
+ * or eight steps are a graph of kernel nodes (base and correction branches
+ * joined where the scheme joins them), replayed until nsteps are enqueued;
+ * stage times and the open-sea elevation are computed on the device from
+ * t0 + k dt. */
 swe_status swe_step(swe_ctx *ctx, int64_t nsteps, double dt);
 
 /* Wait for queued work; returns SWE_ESTATE if a stage produced a non-finite
@@ -218,9 +221,9 @@ const char *swe_last_error(const swe_ctx *ctx);
 /* Upper bound of the device bytes a batch-ready context (uniform order
  * p_max, not separated, not adaptive) with ne elements holds on its own
  * after swe_set_mesh (state, velocity, geometry, order map, scratch, edge
- * items), and of what it takes resident in an empty batch (its share of the
- * pools plus the arrays it keeps); the vertex count is bounded by that of a
- * triangulated polygon with a few holes. */
+ * items, tiles of the one-launch step), and of what it takes resident in an
+ * empty batch (its share of the pools plus the arrays it keeps); the vertex
+ * count is bounded by that of a triangulated polygon with a few holes. */
 int64_t swe_footprint_bytes(int64_t ne, int p_max, int precision);
 
 /* Free everything the context holds; NULL is accepted. */
@@ -228,11 +231,13 @@ void swe_destroy(swe_ctx *ctx);
 
 /* ------------------------------------------------------------------------
  * Batches: many independent instances advanced together.  Every resident
- * instance of one order is covered by one launch per RK stage (one tile per block);
- * each instance keeps its own time, step size, forcing and step budget on
- * the device, so one step graph (built from kernel nodes, no stream capture,
- * and replayed) serves any resident set.  Other host threads may create and
- * fill contexts while a batch runs.
+ * instance of one order is covered by one launch per RK stage (one tile per
+ * block), the orders side by side on streams of the batch's own; each
+ * instance keeps its own time, step size, forcing and step budget on the
+ * device, so one step graph per order (of eight steps, and one for the rest;
+ * built from kernel nodes, no stream capture, and replayed) serves any
+ * resident set.  Other host threads may create and fill contexts while a
+ * batch runs.
  * Members are ordinary contexts (precision equal to the batch's, the fused
  * scheme separate = 0, no extra source) prepared with swe_set_mesh /
  * swe_set_bathymetry / swe_set_open_boundary (at most 4 constituents) /
@@ -250,9 +255,9 @@ void swe_destroy(swe_ctx *ctx);
  * while a pool grows), tile lists, vertex pool, and the arrays a member
  * keeps while resident (vertex and neighbour ids, vertices, flag).  A
  * member's state buffers are released at admission (the pool holds its
- * state) and re-created when it is retired; swe_get_state and swe_mass of a
- * resident member re-create them for the call only.  A pool whose order has
- * no member left is released.
+ * state) and re-created when it is retired; swe_mass of a resident member
+ * re-creates them for the call only, swe_get_state reads the pool.  A pool
+ * whose order has no member left is released.
  * ------------------------------------------------------------------------ */
 typedef struct swe_batch swe_batch;
 

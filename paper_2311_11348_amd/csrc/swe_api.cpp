@@ -1062,7 +1062,12 @@ swe_status build_tiles(swe_ctx *c)
     const int start = fill >= 192 ? 192 : std::max(96, (int)(fill + 7) / 8 * 8), least = fill > 192 ? 128 : 64;
     for (int len = start; len >= least && one_launch_pays(c, len);) {
         const size_t nt = (size_t)((c->ne + len - 1) / len);
-        HIP_TRY(c, hipMalloc(&c->d_tiles, nt * TILE_BYTES));
+        if (hipMalloc(&c->d_tiles, nt * TILE_BYTES) != hipSuccess) {
+            // no room for them: the mesh keeps two launches per step
+            (void)hipGetLastError();
+            c->d_tiles = nullptr;
+            return SWE_OK;
+        }
         TileView t{};
         t.items = static_cast<unsigned *>(c->d_tiles);
         t.meta = reinterpret_cast<int *>(t.items + nt * 2 * BLOCK);
@@ -2057,9 +2062,12 @@ struct swe_batch {
     int grid[4] = {0, 0, 0, 0};
     int ntiles[4] = {0, 0, 0, 0};
     int ncu = 256;
-    hipGraphExec_t gexec = nullptr, multi_exec = nullptr;
-    hipGraph_t graph = nullptr, multi_graph = nullptr;   // one step; GRAPH_STEPS steps
-    int graph_orders = -1;             // bit p set: order p launched by the step graph
+    // per order class: one step and GRAPH_STEPS steps of it as a chain
+    hipGraphExec_t gexec[4] = {}, multi_exec[4] = {};
+    hipGraph_t graph[4] = {}, multi_graph[4] = {};
+    int graph_orders = -1;             // bit p set: order p has a step graph; -1: none built
+    hipStream_t class_s[3] = {};       // streams of the classes after the first, taken when needed
+    hipEvent_t fork = nullptr, join[3] = {};
     std::string err;
 };
 
@@ -2083,12 +2091,14 @@ swe_status bfail(swe_batch *b, swe_status s, const std::string &msg)
 
 void drop_graph(swe_batch *b)
 {
-    if (b->gexec) (void)hipGraphExecDestroy(b->gexec);
-    if (b->graph) (void)hipGraphDestroy(b->graph);
-    if (b->multi_exec) (void)hipGraphExecDestroy(b->multi_exec);
-    if (b->multi_graph) (void)hipGraphDestroy(b->multi_graph);
-    b->gexec = b->multi_exec = nullptr;
-    b->graph = b->multi_graph = nullptr;
+    for (int p = 0; p < 4; ++p) {
+        if (b->gexec[p]) (void)hipGraphExecDestroy(b->gexec[p]);
+        if (b->graph[p]) (void)hipGraphDestroy(b->graph[p]);
+        if (b->multi_exec[p]) (void)hipGraphExecDestroy(b->multi_exec[p]);
+        if (b->multi_graph[p]) (void)hipGraphDestroy(b->multi_graph[p]);
+        b->gexec[p] = b->multi_exec[p] = nullptr;
+        b->graph[p] = b->multi_graph[p] = nullptr;
+    }
     b->graph_orders = -1;
 }
 
@@ -2305,24 +2315,16 @@ hipError_t enqueue_class_step(swe_batch *b, int p, Sink &k)
     return e;
 }
 
-// nsteps steps as a graph of kernel nodes (no stream capture).  Members of
-// different orders share nothing, each order class even has its own clock
-// node, so the classes are branches without a join before the graph's end: a
-// class that fills a part of the chip leaves the rest to the others, and each
-// runs on without waiting for the slowest.  Eight instances of all orders
-// (232,000 elements, FP32): 102 us a step as one chain and one step per
-// graph, now 58.
-hipError_t build_batch_graph(swe_batch *b, int nsteps, hipGraph_t *g_out, hipGraphExec_t *x_out)
+// nsteps steps of order class p as a graph of kernel nodes (no stream capture),
+// one chain.
+hipError_t build_class_graph(swe_batch *b, int p, int nsteps, hipGraph_t *g_out, hipGraphExec_t *x_out)
 {
     hipGraph_t g = nullptr;
     hipError_t e = hipGraphCreate(&g, 0);
     if (e != hipSuccess) return e;
-    for (int p = 0; p < 4 && e == hipSuccess; ++p) {
-        if (b->ntiles[p] == 0) continue;
-        Sink k;
-        k.g = g;
-        for (int s = 0; s < nsteps && e == hipSuccess; ++s) e = enqueue_class_step(b, p, k);
-    }
+    Sink k;
+    k.g = g;
+    for (int s = 0; s < nsteps && e == hipSuccess; ++s) e = enqueue_class_step(b, p, k);
     if (e == hipSuccess) e = hipGraphInstantiate(x_out, g, nullptr, nullptr, 0);
     if (e != hipSuccess) {
         (void)hipGraphDestroy(g);
@@ -2333,11 +2335,15 @@ hipError_t build_batch_graph(swe_batch *b, int nsteps, hipGraph_t *g_out, hipGra
     return hipSuccess;
 }
 
-swe_status build_step_graph(swe_batch *b)
+swe_status build_step_graphs(swe_batch *b)
 {
     drop_graph(b);
-    hipError_t e = build_batch_graph(b, 1, &b->graph, &b->gexec);
-    if (e == hipSuccess) e = build_batch_graph(b, GRAPH_STEPS, &b->multi_graph, &b->multi_exec);
+    hipError_t e = hipSuccess;
+    for (int p = 0; p < 4 && e == hipSuccess; ++p) {
+        if (b->ntiles[p] == 0) continue;
+        e = build_class_graph(b, p, 1, &b->graph[p], &b->gexec[p]);
+        if (e == hipSuccess) e = build_class_graph(b, p, GRAPH_STEPS, &b->multi_graph[p], &b->multi_exec[p]);
+    }
     if (e != hipSuccess) {
         drop_graph(b);
         return bfail(b, SWE_EDEVICE, std::string("step graph: ") + hipGetErrorString(e));
@@ -2345,6 +2351,23 @@ swe_status build_step_graph(swe_batch *b)
     b->graph_orders = 0;
     for (int p = 0; p < 4; ++p) b->graph_orders |= (b->ntiles[p] ? 1 << p : 0) | (b->natiles[p] ? 1 << (4 + p) : 0);
     return SWE_OK;
+}
+
+// The stream of the n-th class present (the first runs on the batch's own),
+// which waits for what the batch's stream holds now; the batch's stream where
+// there is no stream or event to be had.
+hipStream_t fork_class(swe_batch *b, int n)
+{
+    if (n == 0) return b->s;
+    const int i = n - 1;
+    bool ok = b->fork || hipEventCreateWithFlags(&b->fork, hipEventDisableTiming) == hipSuccess;
+    ok = ok && (b->join[i] || hipEventCreateWithFlags(&b->join[i], hipEventDisableTiming) == hipSuccess);
+    ok = ok && (b->class_s[i] || hipStreamCreateWithFlags(&b->class_s[i], hipStreamNonBlocking) == hipSuccess);
+    ok = ok && hipEventRecord(b->fork, b->s) == hipSuccess;
+    ok = ok && hipStreamWaitEvent(b->class_s[i], b->fork, 0) == hipSuccess;
+    if (ok) return b->class_s[i];
+    (void)hipGetLastError();
+    return b->s;
 }
 
 swe_status put_desc(swe_batch *b, int i)
@@ -2479,6 +2502,11 @@ void swe_batch_destroy(swe_batch *b)
     }
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
+    if (b->fork) (void)hipEventDestroy(b->fork);
+    for (int i = 0; i < 3; ++i) {
+        if (b->join[i]) (void)hipEventDestroy(b->join[i]);
+        if (b->class_s[i]) (void)hipStreamDestroy(b->class_s[i]);
+    }
     if (b->own_s) (void)hipStreamDestroy(b->s);
     delete b;
 }
@@ -2615,14 +2643,39 @@ swe_status swe_batch_tick(swe_batch *b, int64_t nsteps)
 {
     if (!b || nsteps < 0) return SWE_EINVAL;
     if (nsteps == 0 || swe_batch_resident(b) == 0) return SWE_OK;
-    if (!b->gexec) {
-        swe_status st = build_step_graph(b);
+    if (b->graph_orders < 0) {
+        swe_status st = build_step_graphs(b);
         if (st) return st;
     }
-    int64_t k = 0;
-    for (; k + GRAPH_STEPS <= nsteps; k += GRAPH_STEPS) BHIP_TRY(b, hipGraphLaunch(b->multi_exec, b->s));
-    for (; k < nsteps; ++k) BHIP_TRY(b, hipGraphLaunch(b->gexec, b->s));
-    return SWE_OK;
+    // Members of different orders share nothing (each class has its own clock
+    // kernel), so the classes run side by side on streams of their own, joined
+    // when the tick's last step is enqueued: a class that fills a part of the
+    // chip leaves the rest to the others.  A replay takes GRAPH_STEPS steps.
+    // Eight instances of all orders (232,000 elements, FP32): 102 us a step as
+    // one chain of every class and one step per replay, now 55; as branches of
+    // one graph 59 and three times the host time (34 us a step), and a served
+    // run whose members came and went ended in a segmentation fault of the host
+    // while such graphs were rebuilt beside other threads' calls.
+    hipStream_t s[4] = {};
+    int n = 0;
+    hipError_t e = hipSuccess;
+    for (int p = 0; p < 4; ++p)
+        if (b->gexec[p]) s[p] = fork_class(b, n++);
+    for (int64_t k = 0; k < nsteps && e == hipSuccess;) {
+        const bool multi = k + GRAPH_STEPS <= nsteps;
+        for (int p = 0; p < 4 && e == hipSuccess; ++p)
+            if (b->gexec[p]) e = hipGraphLaunch(multi ? b->multi_exec[p] : b->gexec[p], s[p]);
+        k += multi ? GRAPH_STEPS : 1;
+    }
+    for (int p = 0; p < 4; ++p)
+        for (int i = 0; i < 3; ++i)
+            if (s[p] && s[p] == b->class_s[i]) {
+                hipError_t j = hipEventRecord(b->join[i], s[p]);
+                if (j == hipSuccess) j = hipStreamWaitEvent(b->s, b->join[i], 0);
+                if (j != hipSuccess) j = hipStreamSynchronize(s[p]);
+                if (e == hipSuccess) e = j;
+            }
+    return e == hipSuccess ? SWE_OK : bfail(b, SWE_EDEVICE, std::string("step graph launch: ") + hipGetErrorString(e));
 }
 
 swe_status swe_batch_sync(swe_batch *b)

@@ -29,9 +29,12 @@
 // order-separated and order-partitioned schemes (k_corr_all, k_full_all,
 // k_epi_all), by teams of four waves per 64 entries or one element per
 // thread, with the correction kernel doing the epilogue's join itself when
-// it runs after the base pass in one chain; the order update (k_indicator,
-// k_apply_order); the batch forms of the stage and order update; the
-// minimum depth control; the FP64 mass reduction.
+// it runs after the base pass in one chain; a whole order-partitioned stage
+// of a smaller mesh in one launch (k_part_all); the order update
+// (k_indicator, k_apply_order); the batch forms of the stage and order
+// update; the minimum depth control; the FP64 mass reduction; the caller's
+// arrays in and out (k_unpack, k_pack).  A uniform order's whole SSP-RK2 step
+// in one launch, built from the same device code, is in swe_step.hip.
 #include "swe_device.h"
 
 #include <algorithm>

@@ -20,7 +20,14 @@ namespace {
 // then the ring.  With 192 owned elements (three waves) the ring of a
 // Morton-ordered triangulation is 35-50 elements and fits the fourth wave,
 // which sits out the second stage's element work: 1.17 times the element
-// work of two separate stages for about half their memory traffic.  Tile
+// work of two separate stages for about half their memory traffic.
+// Bound by VALU issue at FP32 p = 2 (74 % of the SIMDs' cycles), by latency at
+// two blocks and one per CU in FP64 p = 2 and 3.  Two launches / one, us a
+// step: FP32 p = 1 50.3 / 39.8 and p = 2 84.3 / 73.5 (524,288 elements), FP64
+// p = 1 86 / 64 and p = 2 158 / 142 (524,288), 84 / 81 (260,642), p = 3 FP32
+// 33.1 / 26.0 and FP64 49.7 / 38.5 (39,200).  The two stages are unrolled: as
+// a loop the invariants of both live across it (FP64 p = 2 spilled, 110 us
+// at 260,642 elements).  Tile
 // data is built on the device (k_build_tiles) when the mesh is set: edge
 // items, ring and outside neighbours, and the tile's vertices, which are
 // staged in LDS so that neither the edge pass nor the element pass reads
@@ -243,13 +250,15 @@ k_step_sh(StageArgs<Real> a, TileView tv, double xihat2)
 // work): the shorter of two parallel parts leaves the chain.  The roles are
 // separate code from the first load to the last store, so that neither holds
 // the other's registers (joined between the barriers, FP32 p = 2 took 205
-// instead of 130).  Measured at 20,000 elements, us a step with one group of
-// waves / with roles: FP32 p = 1 10.3 / 7.7, p = 2 15.9 / 11.7, p = 3 25.8 /
+// instead of 130).  Measured at 20,000 elements in tiles of 192, us a step with one
+// group of waves / with roles: FP32 p = 1 10.3 / 7.7, p = 2 15.9 / 11.7, p = 3 25.8 /
 // 20.1, FP64 p = 1 12.1 / 9.5, p = 2 20.3 / 17.4 (with two flux groups 18.3);
 // FP64 p = 3 spills with one flux group already (36.7 / 53).  With more tiles
 // than CUs the extra waves cost residency (51,200 elements, FP32 p = 2: 19.5 /
 // 21.3); order 1 fits two blocks of two groups on a CU (65,522 elements, FP32
 // 12.1 / 11.0, FP64 16.4 / 14.8; 96,800: FP32 14.5 / 16.9).
+// Looped over the two stages instead of unrolled, half the code ran 1-5 % slower
+// (p = 3: 25 %, with spills).
 // A block barrier that waves with different roles reach at different places
 // of the code: every wave of the block meets the same number of them, in the
 // same order (the role is uniform over a wave, and the hardware counts waves).
