@@ -49,9 +49,9 @@ Metric: DOF-updates per second per RK stage, DOF = 3 * sum_e K(p_e).  Inputs
 are resident in HBM before the timed region.  Prints one JSON line.
 
 roofline: the headline kernel's algorithmic bytes per launch (11.5 K words +
-100 B per element and stage) over its average launch time in the timed
-region (HIP events on the library stream; every launch there is that
-kernel), against 8 TB/s; traffic: the HBM bytes its counters read per launch
+100 B per element and stage; a launch is a whole step of two stages) over its
+average launch time in the timed region (HIP events on the library stream;
+every launch there is that kernel), against 8 TB/s; traffic: the HBM bytes its counters read per launch
 (a committed counter summary of the same kernel sources), over the same
 time.  compute: the method's floating-point operations per launch over the
 same time, against the vector peaks.  cpu_baseline: the FP64 oracle on the
@@ -93,6 +93,13 @@ def kernel_bytes_per_element(p: int, word: int, nv: int, ne: int) -> float:
     state = (3 * K + 2 * K + 0.5 * 3 * K + 3 * K + 2 * K) * word
     geo = 3 * 4 + 3 * 4 + 1 + 32.0 * nv / ne
     return state + geo
+
+
+def step_bytes_per_element(p: int, word: int, nv: int, ne: int) -> float:
+    """A whole step in one launch: read c and u (5K), write c and u (5K), and
+    the tile's data (4,864 B of edge items, neighbours and vertex ids per 192
+    elements) and the vertex records."""
+    return 10 * K_OF_P[p] * word + 4864 / 192 + 32.0 * nv / ne
 
 
 # Vector peaks of the MI355X (256 CUs at 2.4 GHz): FP32 157.3 TFLOP/s with
@@ -148,7 +155,8 @@ def host_description() -> dict:
             "sockets": len(sockets) or None}
 
 
-KERNEL_SOURCES = ("paper_2311_11348_amd/csrc/swe_kernels.hip", "paper_2311_11348_amd/csrc/swe_internal.h",
+KERNEL_SOURCES = ("paper_2311_11348_amd/csrc/swe_kernels.hip", "paper_2311_11348_amd/csrc/swe_step.hip",
+                  "paper_2311_11348_amd/csrc/swe_device.h", "paper_2311_11348_amd/csrc/swe_internal.h",
                   "paper_2311_11348_amd/csrc/swe_tables.h", "paper_2311_11348_amd/build.py")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_stage_p2_tidal512_traffic.txt")
 BATCH_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "batched64_traffic.txt")
@@ -304,7 +312,7 @@ def timed_steps(ctx, stream, steps, dt):
 
 
 def run_uniform(prob, precision, steps, warmup):
-    """Fused full-order stage kernel on a uniform-order workload."""
+    """Fused full-order kernel on a uniform-order workload."""
     import torch
     from paper_2311_11348_amd import swe
     stream = torch.cuda.Stream()
@@ -320,29 +328,41 @@ def run_uniform(prob, precision, steps, warmup):
     ne, nv = prob.mesh.ne, prob.mesh.nv
     word = 8 if precision == swe.SWE_FP64 else 4
     dof = 3 * K_OF_P[p] * ne
-    # every launch of the timed region is this kernel (two per step, back to back
-    # on the library stream), so the event-timed region / launches is its
-    # average launch duration, launch gaps included
-    launch_s = ms * 1e-3 / (2 * steps)
+    # every launch of the timed region is this kernel (back to back on the
+    # library stream; an odd number of steps ends with two stage launches), so
+    # the event-timed region / launches is its average launch duration, launch
+    # gaps included.  One launch is a whole step (both stages) at orders 1 to 3,
+    # except FP64 p = 3, where the mesh decides: priced per stage
+    whole = 1 <= p <= (2 if word == 8 else 3)
+    stages = 2 if whole else 1
+    stage_s = ms * 1e-3 / (2 * steps)
+    launch_s = stage_s * stages
     bpe = stage_bytes_per_element(p, word)
-    kbpe = kernel_bytes_per_element(p, word, nv, ne)
-    achieved = bpe * ne / launch_s / 1e9
+    kbpe = step_bytes_per_element(p, word, nv, ne) if whole else kernel_bytes_per_element(p, word, nv, ne)
+    achieved = bpe * ne / stage_s / 1e9
     real = "double" if word == 8 else "float"
-    traffic = measured_traffic([f"k_stage_sh<{p}, {real}, {m}>" for m in (1, 2)]) if p == 2 and ne == 524288 else None
-    return {"value": dof / launch_s, "ms_per_step": ms / steps,
+    traffic = measured_traffic([f"k_step_sh<{p}, {real}>"]) if p == 2 and ne == 524288 else None
+    compute = compute_roofline(p, word == 4, ne, stage_s)
+    compute["flop_per_launch"] *= stages
+    return {"value": dof / stage_s, "ms_per_step": ms / steps,
             "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                          "frac": achieved / HBM_PEAK_GBS,
                          "traffic": traffic / 1e9 / launch_s if traffic is not None else None,
                          "traffic_bytes_per_launch": traffic,
-                         "kernel": f"k_stage_sh<{p},{real}> (fused stage, edge fluxes shared within a block)"
+                         "kernel": f"k_step_sh<{p},{real}> (both stages of a step, edge fluxes shared within a tile)"
+                                   if whole else
+                                   f"k_stage_sh<{p},{real}> (fused stage, edge fluxes shared within a block)"
                                    if p >= 1 else f"k_stage<{p},{real}> (fused stage, element gather)",
-                         "bytes_per_element": bpe, "bytes_per_launch": bpe * ne,
+                         "stages_per_launch": stages,
+                         "bytes_per_element": bpe, "bytes_per_launch": bpe * ne * stages,
                          "bytes_note": "11.5 K words + 100 B per element and stage (stored velocity, "
-                                       "c^n read in the second stage only)",
+                                       "c^n read in the second stage only), the method stage by stage; a launch "
+                                       "of both stages keeps the state between them on chip, so its own bytes "
+                                       "(kernel_bytes_per_launch) and counted traffic are lower",
                          "kernel_bytes_per_launch": kbpe * ne,
                          "frac_kernel_bytes": kbpe * ne / launch_s / 1e9 / HBM_PEAK_GBS,
-                         "avg_launch_us": launch_s * 1e6, "launches_timed": 2 * steps},
-            "compute": compute_roofline(p, word == 4, ne, launch_s)}
+                         "avg_launch_us": launch_s * 1e6, "launches_timed": 2 * steps // stages},
+            "compute": compute}
 
 
 def run_separated(prob, precision, steps, warmup, separate=1, chunk=50, hetero=0):
@@ -574,7 +594,8 @@ def run_batched(count, steps, warmup):
                          "frac": ach / HBM_PEAK_GBS,
                          "traffic": step_bytes / (ms32 / steps * 1e-3) / 1e9 if step_bytes else None,
                          "traffic_bytes_per_step": step_bytes,
-                         "kernel": kernel + " + k_batch_clock, whole step (one launch per order class and stage)"},
+                         "kernel": kernel + " + k_batch_clock, whole step (one launch per order class and stage, "
+                                             "the classes side by side)"},
             "fp32_batched": leg(ms32, 4), "fp64_batched": leg(ms64, 8), "plain_fp64": leg(msp, 8),
             "speedup_solves_vs_plain_fp64": msp / ms32,
             "fp32_xi_rel_l2_vs_fp64_max": err, "fp64_batched_vs_plain_xi_rel_l2_max": d64,
