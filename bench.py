@@ -158,7 +158,7 @@ def host_description() -> dict:
 KERNEL_SOURCES = ("paper_2311_11348_amd/csrc/swe_kernels.hip", "paper_2311_11348_amd/csrc/swe_step.hip",
                   "paper_2311_11348_amd/csrc/swe_device.h", "paper_2311_11348_amd/csrc/swe_internal.h",
                   "paper_2311_11348_amd/csrc/swe_tables.h", "paper_2311_11348_amd/build.py")
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_stage_p2_tidal512_traffic.txt")
+TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_step_p2_tidal512_traffic.txt")
 BATCH_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "batched64_traffic.txt")
 
 
