@@ -81,6 +81,7 @@ struct StageArgs {
     // batched instance launched on its own: element indices start at e_off in
     // the pooled arrays; step, open-sea elevation and run flag come from inst
     const struct InstDesc *inst;
+    struct InstDesc *next;         // list kernels up to order 2, last stage of a step: where the next step's clock goes, or null
     int e_off;
     int stage;           // with inst: which stage time of the step (0 or 1) a kernel without MODE uses
     int skip_listed;     // base kernel of the order-partitioned scheme: listed elements are not its work
@@ -236,6 +237,8 @@ hipError_t mass_scratch(double **out);
 int mass_partials(int ne);
 hipError_t launch_batch_stage(int p, bool fp32, int mode, int tile, const BatchArgs &b, int grid, Sink &k);
 // clocks of the instances of one order (order < 0: of every instance)
+// *to = *from advanced by a step (from may equal to)
+hipError_t launch_next_clock(const InstDesc *from, InstDesc *to, const int *flag, Sink &k);
 hipError_t launch_batch_clock(InstDesc *inst, const int *flags, int n, int order, Sink &k);
 // write one instance descriptor in stream order (no host buffer outlives the call)
 hipError_t launch_inst_set(InstDesc *inst, const InstDesc &v, hipStream_t s);

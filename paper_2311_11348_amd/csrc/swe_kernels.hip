@@ -299,6 +299,27 @@ __device__ __forceinline__ void clock_advance(InstDesc &I, int flag)
     I.steps_left -= 1;
 }
 
+// The clock of a step graph's next step, from the current step's: another
+// descriptor, so that a kernel which reads the current one may run meanwhile.
+__device__ __forceinline__ void next_clock(const InstDesc *from, InstDesc *to, const int *flag)
+{
+    if (threadIdx.x != 0) return;
+    *to = *from;
+    clock_advance(*to, flag[0]);
+}
+
+// Whether the list kernels of orders up to PN hold that code, for one block
+// more: order-3 kernels lose scalar registers to it (adaptive tsunami, FP64,
+// 18,818 elements, which does not even use it: 45.8 -> 51.8 us a step), and at
+// p0-1 (204,800 elements) the step took 47.3 instead of 46.4.
+template <int PN>
+constexpr bool clock_in_lists()
+{
+    return PN == 2;
+}
+
+__global__ void k_next_clock(const InstDesc *from, InstDesc *to, const int *flag) { next_clock(from, to, flag); }
+
 __global__ void __launch_bounds__(BLOCK) k_batch_clock(InstDesc *inst, const int *flags, int n, int order)
 {
     const int i = blockIdx.x * BLOCK + threadIdx.x;
@@ -551,6 +572,9 @@ k_full_all(StageArgs<Real> a, int lo, int lcap)
     __builtin_amdgcn_s_setprio(2);
     __shared__ Real sR[3][Ord<PN>::K][PN + 1];
     __shared__ TeamLds<PN, Real> X;
+    if constexpr (clock_in_lists<PN>() && MODE == MODE_STAGE2) {
+        if (a.next && blockIdx.x == gridDim.x - 1) return next_clock(a.inst, a.next, a.flag);
+    }
     full_block<PN, Real, MODE>(a, lo, lcap, (int)blockIdx.x, sR, X);
 }
 
@@ -577,6 +601,9 @@ k_part_all(StageArgs<Real> a, int lcap, int nlist, int nsh, int e_end, const uns
     __shared__ PartLds T;
     if ((int)blockIdx.x < nlist) {
         __builtin_amdgcn_s_setprio(2);
+        if constexpr (clock_in_lists<PN>() && MODE == MODE_STAGE2) {
+            if (a.next && (int)blockIdx.x == nlist - 1) return next_clock(a.inst, a.next, a.flag);
+        }
         full_block<PN, Real, MODE>(a, B, lcap, (int)blockIdx.x, T.L.sR, T.L.X);
         return;
     }
@@ -1514,7 +1541,8 @@ hipError_t full_all_r(int mode, const void *args, int lo, int nblk, int lcap, Si
 {
     StageArgs<Real> a = *static_cast<const StageArgs<Real> *>(args);
     void *kargs[] = {&a, &lo, &lcap};
-    const dim3 g((PN - lo + 1) * list_grid(nblk, PN)), b(TEAM * TEAM_ROLES);
+    // (with a clock to advance, one block more for it)
+    const dim3 g((PN - lo + 1) * list_grid(nblk, PN) + (a.next ? 1 : 0)), b(TEAM * TEAM_ROLES);
     return emit(s,
                 mode == MODE_STAGE1 ? reinterpret_cast<const void *>(&k_full_all<PN, Real, MODE_STAGE1>)
                                     : reinterpret_cast<const void *>(&k_full_all<PN, Real, MODE_STAGE2>),
@@ -1526,8 +1554,9 @@ hipError_t part_all_r(int mode, const void *args, int nblk, int lcap, int nsh, i
                       const int *item_off, Sink &s)
 {
     StageArgs<Real> a = *static_cast<const StageArgs<Real> *>(args);
-    // (a multiple of 8, so that the base blocks keep their XCDs)
-    int nlist = ((PN - B + 1) * list_grid(nblk, PN) + 7) / 8 * 8;
+    // (a multiple of 8, so that the base blocks keep their XCDs; the last is past
+    // every list's end where there is a clock to advance)
+    int nlist = ((PN - B + 1) * list_grid(nblk, PN) + (a.next ? 8 : 7)) / 8 * 8;
     void *kargs[] = {&a, &lcap, &nlist, &nsh, &e_end, &items, &item_off};
     return emit(s,
                 mode == MODE_STAGE1 ? reinterpret_cast<const void *>(&k_part_all<B, PN, Real, MODE_STAGE1>)
@@ -1763,6 +1792,12 @@ hipError_t launch_place_items(const unsigned *items, const int *item_off, int nb
     if (first % BLOCK != 0 || !pool.items || !pool.nitems) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_place_items, dim3(nblk), dim3(BLOCK), 0, s, items, item_off, pool, first);
     return hipGetLastError();
+}
+
+hipError_t launch_next_clock(const InstDesc *from, InstDesc *to, const int *flag, Sink &k)
+{
+    void *kargs[] = {&from, &to, &flag};
+    return emit(k, reinterpret_cast<const void *>(&k_next_clock), dim3(1), dim3(64), kargs);
 }
 
 hipError_t launch_batch_clock(InstDesc *inst, const int *flags, int n, int order, Sink &k)
