@@ -391,6 +391,7 @@ hipError_t enqueue_one_launch_step(Lanes &L, int in, double tn, double dt)
     a.Cout = static_cast<Real *>(c->d_C[1 - in]);
     a.Uout = static_cast<Real *>(c->d_U[1 - in]);
     L.time(a, 0, tn, dt);
+    a.stage = in;
     return launch_step_sh(c->cfg.p_max, c->fp32, &a, c->tiles, L.graph ? 0.0 : xi_hat(c, tn + dt), c->ncu,
                           L.a);
 }

@@ -83,7 +83,8 @@ struct StageArgs {
     const struct InstDesc *inst;
     struct InstDesc *next;         // list kernels up to order 2, last stage of a step: where the next step's clock goes, or null
     int e_off;
-    int stage;           // with inst: which stage time of the step (0 or 1) a kernel without MODE uses
+    int stage;           // with inst: which stage time of the step (0 or 1) a kernel without MODE uses;
+                         // one-launch step: 1 for the second of a pair, whose result goes to state buffer 0
     int skip_listed;     // base kernel of the order-partitioned scheme: listed elements are not its work
     int blocks;          // stage launchers: cover the first blocks * BLOCK elements only (0: all)
 };
@@ -108,6 +109,7 @@ struct InstDesc {
     int first, ne, vbase, nv;
     int order;
     int active, run;             // resident / advancing in the current step
+    int ran;                     // run of the step before
     int steps_done, steps_left;
     int ncon;
     int mixed;                   // per-element orders (pool ep) mask the stage

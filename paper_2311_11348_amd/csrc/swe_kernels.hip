@@ -290,6 +290,7 @@ __device__ __forceinline__ double clock_xihat(const InstDesc &I, double t)
 __device__ __forceinline__ void clock_advance(InstDesc &I, int flag)
 {
     const int run = I.active && I.steps_left > 0 && flag == 0;
+    I.ran = I.run;
     I.run = run;
     if (!run) return;
     I.xh[0] = clock_xihat(I, I.t);

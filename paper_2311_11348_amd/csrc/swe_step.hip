@@ -215,6 +215,26 @@ __device__ __forceinline__ void step_tile(StepLds<P, Real, false> &T, const Stag
     (void)store_state<P, Real, CPOL_THROUGH>(a, off, s.xi, s.U, s.V, s.u, s.v);
 }
 
+// A stopped step (failure in an earlier one).  The state rests in buffer 0:
+// where the step before was the last to run and left its result in buffer 1
+// (it was the first of a pair), the second of the pair carries it over.
+// Thread l of the block takes the tile's owned element l.
+template <int P, typename Real>
+__device__ __forceinline__ void stopped_step(const StageArgs<Real> &a, int len)
+{
+    constexpr int K = Ord<P>::K;
+    const int l = (int)threadIdx.x, e = xcd_block(blockIdx.x, gridDim.x) * len + l;
+    if (!a.stage || !a.inst->ran || l >= len || e >= a.m.ne) return;
+    const unsigned off = (unsigned)e * (unsigned)sizeof(Real);
+    const int KS = a.m.KS, stride = a.m.stride;
+    const Buf<Real> bC(a.Cin, 3 * KS, stride), bU(a.Uin, 2 * KS, stride);
+    const Buf<Real> oC(a.Cout, 3 * KS, stride), oU(a.Uout, 2 * KS, stride);
+#pragma unroll 1
+    for (int q = 0; q < 3 * K; ++q) oC.st(q, off, bC.ld(q, off));
+#pragma unroll 1
+    for (int q = 0; q < 2 * K; ++q) oU.st(q, off, bU.ld(q, off));
+}
+
 template <int P, typename Real>
 constexpr int step_waves()
 {
@@ -231,7 +251,7 @@ k_step_sh(StageArgs<Real> a, TileView tv, double xihat2)
     double xh0 = a.xihat, xh1 = xihat2, dt = a.dt;
     if (a.inst) {
         // the step's clock stopped (failure): the whole block leaves before its first barrier
-        if (!a.inst->run) return;
+        if (!a.inst->run) return stopped_step<P, Real>(a, tv.len);
         xh0 = a.inst->xh[0];
         xh1 = a.inst->xh[1];
         dt = a.inst->dt;
@@ -402,7 +422,8 @@ k_step_roles(StageArgs<Real> a, TileView tv, double xihat2)
     load_trace_lds<P, Real, true>(T.S);
     double xh0 = a.xihat, xh1 = xihat2, dt = a.dt;
     if (a.inst) {
-        if (!a.inst->run) return;   // the step's clock stopped (failure); uniform over the block
+        // the step's clock stopped (failure); uniform over the block
+        if (!a.inst->run) return stopped_step<P, Real>(a, tv.len);
         xh0 = a.inst->xh[0];
         xh1 = a.inst->xh[1];
         dt = a.inst->dt;
