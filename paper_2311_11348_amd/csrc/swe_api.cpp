@@ -294,12 +294,13 @@ struct Lanes {
     bool graph = false, chain = false;
     const InstDesc *inst = nullptr;   // graph: the current step's clock
     InstDesc *next = nullptr;         // and where the step's last list kernel puts the next one's, or null
+    int *flag = nullptr;              // and where its failures go
     explicit Lanes(swe_ctx *cc) : c(cc)
     {
         a.s = c->s_base;
         b.s = c->s_corr;
     }
-    Lanes(swe_ctx *cc, hipGraph_t g) : c(cc), graph(true), chain(one_chain(cc)), inst(cc->d_inst)
+    Lanes(swe_ctx *cc, hipGraph_t g) : c(cc), graph(true), chain(one_chain(cc)), inst(cc->d_inst), flag(cc->d_flag)
     {
         a.g = g;
         b.g = g;
@@ -335,6 +336,7 @@ struct Lanes {
     {
         if (graph) {
             args.inst = inst;
+            args.flag = flag;
             args.stage = stage;
         } else {
             args.xihat = xi_hat(c, t);
@@ -658,7 +660,10 @@ hipError_t enqueue_depth_limit(Lanes &L, int out)
     StageArgs<Real> a = make_args<Real>(c);
     a.Cout = static_cast<Real *>(c->d_C[out]);
     a.Uout = static_cast<Real *>(c->d_U[out]);
-    if (L.graph) a.inst = L.inst;
+    if (L.graph) {
+        a.inst = L.inst;
+        a.flag = L.flag;
+    }
     return launch_depth_limit(c->cfg.p_max, c->fp32, &a, c->cfg.h_min, L.a);
 }
 
@@ -718,13 +723,15 @@ hipError_t build_graph(swe_ctx *c, int nsteps, hipGraph_t *g_out, hipGraphExec_t
         // leaves its last step's there).  As a kernel between joined stages it
         // cost another dispatch (static p1-2, us a step: FP64 16,200 elements
         // 21.8 -> 20.5, 204,800 76.4 -> 72.0, 2,097,152 499 -> 495, FP32
-        // 204,800 48.5 -> 46.8).
+        // 204,800 48.5 -> 46.8).  Such a step reports failures to the next
+        // one's clock (see step_stopped); the graph's last to the run's flag.
         if (!c->cfg.adapt) {
             const bool listed = separated(c) && c->cfg.separate == 2 && c->cfg.p_max == 2 && list_blocks(c) > 0;
             InstDesc *now = c->d_inst + (listed ? (nsteps - 1 - s) & 1 : 0);
             if (s == 0 || !listed) e = launch_next_clock(c->d_inst, now, c->d_flag, L.a);
             L.inst = now;
             L.next = listed && s + 1 < nsteps ? c->d_inst + ((nsteps - 2 - s) & 1) : nullptr;
+            L.flag = L.next ? &L.next->late : c->d_flag;
         }
         if (e == hipSuccess) e = c->fp32 ? enqueue_step_of<float>(L, s, paired, 0.0, 0.0)
                                          : enqueue_step_of<double>(L, s, paired, 0.0, 0.0);

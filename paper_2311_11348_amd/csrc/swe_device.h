@@ -804,6 +804,20 @@ __device__ __forceinline__ Real store_state(const StageArgs<Real> &a, unsigned o
     return chk;
 }
 
+// Whether the step of a step graph does not run: its clock stopped, or the step
+// before failed when this step's clock was already set (the list kernel that
+// sets it runs beside kernels which may still find a failure; they write it to
+// the next clock's `late`, which is final when the next step starts).  A step
+// that does not run for the latter reason reports a failure itself, so that the
+// one after it does not run either.  Uniform over the grid.
+template <typename Real>
+__device__ __forceinline__ bool step_stopped(const StageArgs<Real> &a)
+{
+    if (a.inst->run && !a.inst->late) return false;
+    if (a.inst->late) a.flag[0] = 1;
+    return true;
+}
+
 // SSP-RK2 combine of acc = c + dt L, u-solve of the new state, store, depth check
 template <int P, typename Real, int MODE>
 __device__ __forceinline__ void finish_stage(const StageArgs<Real> &a, unsigned e, const Geo &G,

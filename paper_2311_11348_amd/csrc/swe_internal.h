@@ -82,6 +82,7 @@ struct StageArgs {
     // the pooled arrays; step, open-sea elevation and run flag come from inst
     const struct InstDesc *inst;
     struct InstDesc *next;         // list kernels up to order 2, last stage of a step: where the next step's clock goes, or null
+                                   // (flag is then its `late`)
     int e_off;
     int stage;           // with inst: which stage time of the step (0 or 1) a kernel without MODE uses;
                          // one-launch step: 1 for the second of a pair, whose result goes to state buffer 0
@@ -109,6 +110,7 @@ struct InstDesc {
     int first, ne, vbase, nv;
     int order;
     int active, run;             // resident / advancing in the current step
+    int late;                    // the step before failed after this clock was set: the current step does not run
     int ran;                     // run of the step before
     int steps_done, steps_left;
     int ncon;
@@ -238,9 +240,9 @@ hipError_t launch_mass_noalloc(const MeshView &m, bool fp32, const void *C, doub
 hipError_t mass_scratch(double **out);
 int mass_partials(int ne);
 hipError_t launch_batch_stage(int p, bool fp32, int mode, int tile, const BatchArgs &b, int grid, Sink &k);
+// *to = *from advanced by a step (from may equal to), both with `late` clear
+hipError_t launch_next_clock(InstDesc *from, InstDesc *to, const int *flag, Sink &k);
 // clocks of the instances of one order (order < 0: of every instance)
-// *to = *from advanced by a step (from may equal to)
-hipError_t launch_next_clock(const InstDesc *from, InstDesc *to, const int *flag, Sink &k);
 hipError_t launch_batch_clock(InstDesc *inst, const int *flags, int n, int order, Sink &k);
 // write one instance descriptor in stream order (no host buffer outlives the call)
 hipError_t launch_inst_set(InstDesc *inst, const InstDesc &v, hipStream_t s);

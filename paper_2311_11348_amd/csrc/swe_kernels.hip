@@ -55,7 +55,7 @@ k_stage_sh(StageArgs<Real> a, const unsigned *items, const int *item_off)
     double xihat = a.xihat, dt = a.dt;
     if (a.inst) {
         // the step's clock stopped (failure): the whole block leaves before its first barrier
-        if (!a.inst->run) return;
+        if (step_stopped(a)) return;
         xihat = MODE == MODE_STAGE2 ? a.inst->xh[1] : a.inst->xh[0];
         dt = a.inst->dt;
     }
@@ -136,7 +136,7 @@ k_stage(StageArgs<Real> a)
     double xihat = a.xihat, dt = a.dt;
     if (a.inst) {
         // one instance of a batch: its clock lives on the device
-        if (!a.inst->run) return;
+        if (step_stopped(a)) return;
         xihat = MODE == MODE_STAGE2 ? a.inst->xh[1] : a.inst->xh[0];
         dt = a.inst->dt;
     }
@@ -302,11 +302,19 @@ __device__ __forceinline__ void clock_advance(InstDesc &I, int flag)
 
 // The clock of a step graph's next step, from the current step's: another
 // descriptor, so that a kernel which reads the current one may run meanwhile.
-__device__ __forceinline__ void next_clock(const InstDesc *from, InstDesc *to, const int *flag)
+// It holds the run's constants already.  Failures of the current step are
+// still being found, so the flag is not looked at (see step_stopped).
+__device__ __forceinline__ void next_clock(const InstDesc *from, InstDesc *to)
 {
     if (threadIdx.x != 0) return;
-    *to = *from;
-    clock_advance(*to, flag[0]);
+    InstDesc v = *from;
+    clock_advance(v, !v.run);
+    to->run = v.run;
+    to->steps_done = v.steps_done;
+    to->steps_left = v.steps_left;
+    to->t = v.t;
+    to->xh[0] = v.xh[0];
+    to->xh[1] = v.xh[1];
 }
 
 // Whether the list kernels of orders up to PN hold that code, for one block
@@ -319,7 +327,13 @@ constexpr bool clock_in_lists()
     return PN == 2;
 }
 
-__global__ void k_next_clock(const InstDesc *from, InstDesc *to, const int *flag) { next_clock(from, to, flag); }
+__global__ void k_next_clock(InstDesc *from, InstDesc *to, const int *flag)
+{
+    if (threadIdx.x != 0) return;
+    if (to != from) *to = *from;
+    clock_advance(*to, flag[0]);
+    from->late = to->late = 0;
+}
 
 __global__ void __launch_bounds__(BLOCK) k_batch_clock(InstDesc *inst, const int *flags, int n, int order)
 {
@@ -533,7 +547,7 @@ __device__ __forceinline__ void full_block(const StageArgs<Real> &a, int lo, int
     if (c * (team ? TEAM : BLOCK) >= len) return;
     double xihat = a.xihat, dt = a.dt;
     if (a.inst) {
-        if (!a.inst->run) return;   // the step's clock stopped (failure); uniform over the block
+        if (step_stopped(a)) return;   // the step's clock stopped (failure); uniform over the block
         xihat = MODE == MODE_STAGE2 ? a.inst->xh[1] : a.inst->xh[0];
         dt = a.inst->dt;
     }
@@ -574,7 +588,7 @@ k_full_all(StageArgs<Real> a, int lo, int lcap)
     __shared__ Real sR[3][Ord<PN>::K][PN + 1];
     __shared__ TeamLds<PN, Real> X;
     if constexpr (clock_in_lists<PN>() && MODE == MODE_STAGE2) {
-        if (a.next && blockIdx.x == gridDim.x - 1) return next_clock(a.inst, a.next, a.flag);
+        if (a.next && blockIdx.x == gridDim.x - 1) return next_clock(a.inst, a.next);
     }
     full_block<PN, Real, MODE>(a, lo, lcap, (int)blockIdx.x, sR, X);
 }
@@ -603,7 +617,7 @@ k_part_all(StageArgs<Real> a, int lcap, int nlist, int nsh, int e_end, const uns
     if ((int)blockIdx.x < nlist) {
         __builtin_amdgcn_s_setprio(2);
         if constexpr (clock_in_lists<PN>() && MODE == MODE_STAGE2) {
-            if (a.next && (int)blockIdx.x == nlist - 1) return next_clock(a.inst, a.next, a.flag);
+            if (a.next && (int)blockIdx.x == nlist - 1) return next_clock(a.inst, a.next);
         }
         full_block<PN, Real, MODE>(a, B, lcap, (int)blockIdx.x, T.L.sR, T.L.X);
         return;
@@ -612,7 +626,7 @@ k_part_all(StageArgs<Real> a, int lcap, int nlist, int nsh, int e_end, const uns
     const int blk = xcd_block((int)blockIdx.x - nlist, (int)gridDim.x - nlist);
     double xihat = a.xihat, dt = a.dt;
     if (a.inst) {
-        if (!a.inst->run) return;   // the step's clock stopped (failure); uniform over the block
+        if (step_stopped(a)) return;   // the step's clock stopped (failure); uniform over the block
         xihat = MODE == MODE_STAGE2 ? a.inst->xh[1] : a.inst->xh[0];
         dt = a.inst->dt;
     }
@@ -1197,7 +1211,7 @@ __global__ void __launch_bounds__(BLOCK) k_depth_limit(StageArgs<Real> a, double
     const MeshView &m = a.m;
     const unsigned e = blockIdx.x * BLOCK + threadIdx.x;
     if (e >= (unsigned)m.ne) return;
-    if (a.inst && !a.inst->run) return;   // the step's clock stopped (failure)
+    if (a.inst && step_stopped(a)) return;   // the step's clock stopped (failure)
     const int p = m.ep ? (int)m.ep[e] : PM;
     if (p < 1) return;
     const int Ke = KOFP[p];
@@ -1795,7 +1809,7 @@ hipError_t launch_place_items(const unsigned *items, const int *item_off, int nb
     return hipGetLastError();
 }
 
-hipError_t launch_next_clock(const InstDesc *from, InstDesc *to, const int *flag, Sink &k)
+hipError_t launch_next_clock(InstDesc *from, InstDesc *to, const int *flag, Sink &k)
 {
     void *kargs[] = {&from, &to, &flag};
     return emit(k, reinterpret_cast<const void *>(&k_next_clock), dim3(1), dim3(64), kargs);

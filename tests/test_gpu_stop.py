@@ -67,3 +67,48 @@ def test_uniform_stop(n, p, precision):
         seen.add(want[0] % 2)
         assert np.array_equal(stopped(make, c0, dt), want[1], equal_nan=True), (k, want[0])
     assert seen == {0, 1}
+
+
+def first_stage_passes(prob, precision, c, dt):
+    """Whether c + dt L(c) is finite with a positive mean depth in every element."""
+    with swe.context_for(prob, precision=precision) as ctx:
+        c1 = c + dt * ctx.rhs(0.0, c)
+    H = c1[:, 0, 0] / np.sqrt(prob.mesh.areas()) + prob.hb_vertex[prob.mesh.tri].mean(axis=1)
+    return bool(np.all(np.isfinite(c1)) and np.all(H > 0.0))
+
+
+# The order-partitioned graphs whose clock advances in the list kernel of the
+# step before, while the rest of that step's last stage may still find a
+# failure: each stage in one launch, and (more than 448 base blocks in FP64,
+# 1,536 in FP32) its kernels on branches.  c0 of a step that first fails in its
+# second stage is made by the scan over time steps.
+@pytest.mark.parametrize("precision,n,lo", [(swe.SWE_FP64, 20, 1), (swe.SWE_FP32_WB, 20, 1), (swe.SWE_FP64, 20, 0),
+                                            (swe.SWE_FP64, 260, 1), (swe.SWE_FP32_WB, 480, 1)])
+def test_partitioned_stop(precision, n, lo):
+    prob = basin(n, lo, 2)
+    order = prob.p
+    c0 = I.random_state(prob.mesh, prob.p, 2, 3, prob.hb_vertex, 0.2, 0.5, 0.1)
+
+    def make(graph):
+        ctx = swe.context_for(prob, precision=precision, separate=2, step_graph=graph)
+        ctx.set_order(order)
+        return ctx
+
+    small = n < 100
+    seen, second = set(), 0
+    for k in range(16 if small else 6):
+        dt = prob.dt() * (3.0 * 1.2 ** k if small else 7.0 * 1.25 ** k)
+        want = expected(make, c0, dt)
+        if want is None:
+            continue
+        step, state = want
+        seen.add(step)
+        with make(0) as ctx:
+            ctx.set_state(c0)
+            for _ in range(step - 1):
+                ctx.step(1, dt)
+            before = ctx.state()[0]
+        second += first_stage_passes(prob, precision, before, dt)
+        for _ in range(3):
+            assert np.array_equal(stopped(make, c0, dt), state, equal_nan=True), (k, step)
+    assert len(seen) > 1 and second > 0
