@@ -842,8 +842,10 @@ swe_status upload_state(swe_ctx *c, const double *coef, void *dst)
 
 // Pinned host memory for read-backs, one per process: RING_SLOTS slots, taken
 // at the first read-back of RING_FROM bytes and given back when the last
-// context goes.  One thread uses it at a time (a read-back that finds it busy
-// goes through the device staging buffer instead).
+// context goes; coherent by its own flag, since kernels write it and host
+// threads read it (the default is the environment's to set).  One thread uses
+// it at a time (a read-back that finds it busy goes through the device staging
+// buffer instead).
 constexpr size_t RING_SLOT = 4u << 20, RING_FROM = 1u << 20;
 constexpr int RING_SLOTS = 4, RING_THREADS = 4;
 std::mutex ring_use, ring_count;
@@ -876,8 +878,9 @@ hipError_t ring_download(swe_ctx *c, const void *src, int stride, int first, int
     const size_t row = sizeof(double) * (size_t)n;
     hipEvent_t ev[RING_SLOTS] = {};
     hipError_t e = hipSuccess;
+    // (the host reads the slot after the event: a release to the system)
     for (auto &x : ev)
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&x, hipEventDisableTiming);
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&x, hipEventDisableTiming | hipEventReleaseToSystem);
     std::atomic<int64_t> packed{0};             // parts in their slots
     std::atomic<bool> stop{false};
     std::vector<std::atomic<int>> copied((size_t)parts);
@@ -955,7 +958,7 @@ swe_status download(swe_ctx *c, const void *src, int stride, int first, int ncom
         if (u.owns_lock()) {
             if (!ring_mem && sizeof(double) * n * (size_t)c->ne >= RING_FROM) {
                 void *q = nullptr;
-                if (hipHostMalloc(&q, RING_SLOTS * RING_SLOT, hipHostMallocPortable) == hipSuccess)
+                if (hipHostMalloc(&q, RING_SLOTS * RING_SLOT, hipHostMallocPortable | hipHostMallocCoherent) == hipSuccess)
                     ring_mem = static_cast<char *>(q);
                 else
                     (void)hipGetLastError();
