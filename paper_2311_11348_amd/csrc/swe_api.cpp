@@ -883,16 +883,16 @@ hipError_t ring_download(swe_ctx *c, const void *src, int stride, int first, int
         if (e == hipSuccess) e = hipEventCreateWithFlags(&x, hipEventDisableTiming | hipEventReleaseToSystem);
     std::atomic<int64_t> packed{0};             // parts in their slots
     std::atomic<bool> stop{false};
-    std::vector<std::atomic<int>> copied((size_t)parts);
+    std::atomic<int64_t> copied[RING_SLOTS];    // of each slot: copies made by any thread, nth per part
     for (auto &x : copied) x.store(0);
-    std::vector<std::thread> pool;
+    std::thread pool[RING_THREADS - 1];         // (nothing here allocates outside the try below)
     int nth = 1;
     auto copy = [&](int64_t i, int t) {
         // thread t's share of part i
         const size_t lo = row * (size_t)(i * per), hi = row * (size_t)std::min<int64_t>(c->ne, (i + 1) * per);
         const size_t a = (hi - lo) * (size_t)t / (size_t)nth, b = (hi - lo) * (size_t)(t + 1) / (size_t)nth;
         std::memcpy(reinterpret_cast<char *>(out) + lo + a, ring_mem + (size_t)(i % RING_SLOTS) * RING_SLOT + a, b - a);
-        copied[(size_t)i].fetch_add(1, std::memory_order_release);
+        copied[i % RING_SLOTS].fetch_add(1, std::memory_order_release);
     };
     auto work = [&](int t) {
         for (int64_t i = 0; i < parts; ++i) {
@@ -906,23 +906,23 @@ hipError_t ring_download(swe_ctx *c, const void *src, int stride, int first, int
     // the share sizes depend on how many threads there are: all start first
     const int want = parts >= 2 ? std::min<int>(RING_THREADS, std::max(1u, std::thread::hardware_concurrency())) : 1;
     std::atomic<bool> go{false};
+    int started = 1;
     try {
-        pool.reserve((size_t)want);
-        for (int t = 1; t < want; ++t)
-            pool.emplace_back([&, t] {
+        for (; started < want; ++started)
+            pool[started - 1] = std::thread([&, t = started] {
                 while (!go.load(std::memory_order_acquire)) std::this_thread::yield();
                 work(t);
             });
     } catch (...) {
         // fewer threads
     }
-    nth = 1 + (int)pool.size();
+    nth = started;
     go.store(true, std::memory_order_release);
     int64_t enq = 0;
     for (int64_t i = 0; i < parts && e == hipSuccess; ++i) {
         // pack ahead into every slot whose last part all threads have copied
         while (enq < parts && enq - i < RING_SLOTS && e == hipSuccess) {
-            if (enq >= RING_SLOTS && copied[(size_t)(enq - RING_SLOTS)].load(std::memory_order_acquire) < nth) {
+            if (copied[enq % RING_SLOTS].load(std::memory_order_acquire) < nth * (enq / RING_SLOTS)) {
                 if (enq > i) break;
                 std::this_thread::yield();
                 continue;
@@ -940,7 +940,8 @@ hipError_t ring_download(swe_ctx *c, const void *src, int stride, int first, int
         copy(i, 0);
     }
     if (e != hipSuccess) stop.store(true);
-    for (auto &t : pool) t.join();
+    for (auto &t : pool)
+        if (t.joinable()) t.join();
     if (e != hipSuccess) (void)hipStreamSynchronize(c->s_base);   // no kernel still writes a slot
     for (auto &x : ev)
         if (x) (void)hipEventDestroy(x);

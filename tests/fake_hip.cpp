@@ -33,6 +33,14 @@ std::map<void *, size_t> sizes;
 std::atomic<int> in_graph_call{0};
 thread_local bool refuse = false;
 
+// held while the maps above are used, whose own allocations are not refused
+struct Model {
+    std::lock_guard<std::mutex> lock{mx};
+    const bool was = refuse;
+    Model() { refuse = false; }
+    ~Model() { refuse = was; }
+};
+
 void done(void *s, long n)
 {
     Stream &t = streams[s];
@@ -46,7 +54,7 @@ struct GraphCall {
     GraphCall()
     {
         const int n = ++in_graph_call;
-        std::lock_guard<std::mutex> l(mx);
+        Model l;
         if (n > counts["graph calls at once"]) counts["graph calls at once"] = n;
     }
     ~GraphCall()
@@ -59,7 +67,7 @@ struct GraphCall {
 hipError_t alloc(void **p, size_t n)
 {
     *p = calloc(1, n ? n : 1);
-    std::lock_guard<std::mutex> l(mx);
+    Model l;
     sizes[*p] = n;
     counts["bytes"] += (long)n;
     counts["allocations"] += 1;
@@ -69,7 +77,7 @@ hipError_t alloc(void **p, size_t n)
 hipError_t release(void *p)
 {
     {
-        std::lock_guard<std::mutex> l(mx);
+        Model l;
         counts["bytes"] -= (long)sizes[p];
         sizes.erase(p);
     }
@@ -100,7 +108,7 @@ extern "C" {
 
 long fake_count(const char *what)
 {
-    std::lock_guard<std::mutex> l(mx);
+    Model l;
     return counts[what];
 }
 void fake_refuse_new(int on) { refuse = on != 0; }
@@ -109,7 +117,7 @@ hipError_t hipMalloc(void **p, size_t n) { return alloc(p, n); }
 hipError_t hipFree(void *p) { return release(p); }
 hipError_t hipHostMalloc(void **p, size_t n, unsigned flags)
 {
-    std::lock_guard<std::mutex> l(mx);
+    Model l;
     counts["pinned allocations"] += 1;
     if (!(flags & hipHostMallocCoherent)) counts["pinned allocations not coherent"] += 1;
     *p = calloc(1, n);
@@ -143,7 +151,7 @@ hipError_t hipStreamDestroy(hipStream_t s)
 }
 hipError_t hipStreamSynchronize(hipStream_t s)
 {
-    std::lock_guard<std::mutex> l(mx);
+    Model l;
     done(s, streams[s].issued);
     return hipSuccess;
 }
@@ -155,14 +163,14 @@ hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *st)
 hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode *) { return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned)
 {
-    std::lock_guard<std::mutex> l(mx);
+    Model l;
     for (const auto &w : events[e]) streams[s].waits.insert(w);
     return hipSuccess;
 }
 hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned flags)
 {
     handle(e);
-    std::lock_guard<std::mutex> l(mx);
+    Model l;
     event_flags[*e] = flags;
     return hipSuccess;
 }
@@ -174,14 +182,14 @@ hipError_t hipEventDestroy(hipEvent_t e)
 }
 hipError_t hipEventRecord(hipEvent_t e, hipStream_t s)
 {
-    std::lock_guard<std::mutex> l(mx);
+    Model l;
     events[e] = Waits{{s, streams[s].issued}};
     for (const auto &w : streams[s].waits) events[e].insert(w);
     return hipSuccess;
 }
 hipError_t hipEventSynchronize(hipEvent_t e)
 {
-    std::lock_guard<std::mutex> l(mx);
+    Model l;
     if (!(event_flags[e] & hipEventReleaseToSystem)) counts["host waits on events without a system release"] += 1;
     for (const auto &w : Waits(events[e])) done(w.first, w.second);
     return hipSuccess;
@@ -229,7 +237,7 @@ hipError_t hipGraphInstantiate(hipGraphExec_t *x, hipGraph_t, hipGraphNode_t *, 
 {
     GraphCall call;
     handle(x);
-    std::lock_guard<std::mutex> l(mx);
+    Model l;
     counts["graphs built"] += 1;
     execs[*x].clear();
     return hipSuccess;
@@ -237,7 +245,7 @@ hipError_t hipGraphInstantiate(hipGraphExec_t *x, hipGraph_t, hipGraphNode_t *, 
 hipError_t hipGraphExecDestroy(hipGraphExec_t x)
 {
     GraphCall call;
-    std::lock_guard<std::mutex> l(mx);
+    Model l;
     for (const auto &w : execs[x])
         if (streams[w.first].done < w.second) counts["graphs destroyed in flight"] += 1;
     execs.erase(x);
@@ -246,7 +254,7 @@ hipError_t hipGraphExecDestroy(hipGraphExec_t x)
 }
 hipError_t hipGraphLaunch(hipGraphExec_t x, hipStream_t s)
 {
-    std::lock_guard<std::mutex> l(mx);
+    Model l;
     execs[x].insert({s, ++streams[s].issued});
     return hipSuccess;
 }
@@ -257,14 +265,14 @@ namespace swe {
 
 hipError_t launch_build_tiles(const MeshView &, int, const TileView &, int *, hipStream_t)
 {
-    std::lock_guard<std::mutex> l(mx);
+    Model l;
     counts["tile builds"] += 1;
     return hipSuccess;
 }
 bool stage_sh_supported(int p, bool) { return p >= 1; }
 hipError_t launch_step_sh(int, bool, const void *, const TileView &, double, int, Sink &)
 {
-    std::lock_guard<std::mutex> l(mx);
+    Model l;
     counts["one-launch steps"] += 1;
     return hipSuccess;
 }

@@ -19,3 +19,17 @@ def test_read_back_memory_is_coherent_by_its_own_flags(lib):
             assert count("pinned allocations not coherent") == 0
             assert count("host waits on events without a system release") == 0
     """)
+
+
+def test_read_back_without_host_memory_does_not_throw(lib):
+    """An exception that leaves the C entry ends the process."""
+    host_runtime.run(lib, """
+        with swe.context_for(I.config_c2(n=160, p=2)) as ctx:
+            out, t = np.empty((ctx.ne, 3, ctx.K)), ctypes.c_double()
+            for _ in range(2):                                     # the ring's first use, then a later one
+                L.fake_refuse_new(1)
+                st = L.swe_get_state(ctx.h, swe._d(out), ctypes.byref(t))
+                L.fake_refuse_new(0)
+                assert st == swe.SWE_OK, st
+            assert count("pinned allocations") == 1
+    """)
