@@ -138,8 +138,17 @@ hipError_t d2h(swe_ctx *c, void *dst, const void *src, size_t bytes)
 
 hipError_t dzero(swe_ctx *c, void *dst, size_t bytes) { return hipMemsetAsync(dst, 0, bytes, c->s_base); }
 
+// Step graphs are built and destroyed by one thread of the process at a time,
+// and destroyed only when their replays are over (every caller has waited for
+// the stream since the last one).  A served run in which branched graphs were
+// rebuilt beside other threads' calls ended in a fault of the host whose cause
+// is not known; a mesh with a static order map still has branches.
+std::mutex graph_calls;
+
 void drop_step_graph(swe_ctx *c)
 {
+    if (!c->step_exec && !c->step_graph && !c->multi_exec && !c->multi_graph) return c->graph_key.clear();
+    std::lock_guard<std::mutex> one(graph_calls);
     if (c->step_exec) (void)hipGraphExecDestroy(c->step_exec);
     if (c->step_graph) (void)hipGraphDestroy(c->step_graph);
     if (c->multi_exec) (void)hipGraphExecDestroy(c->multi_exec);
@@ -711,6 +720,7 @@ constexpr int GRAPH_STEPS = 8;
 
 hipError_t build_graph(swe_ctx *c, int nsteps, hipGraph_t *g_out, hipGraphExec_t *x_out)
 {
+    std::lock_guard<std::mutex> one(graph_calls);
     hipGraph_t g = nullptr;
     hipError_t e = hipGraphCreate(&g, 0);
     if (e != hipSuccess) return e;
@@ -2119,6 +2129,11 @@ swe_status bfail(swe_batch *b, swe_status s, const std::string &msg)
 
 void drop_graph(swe_batch *b)
 {
+    bool any = false;
+    for (int p = 0; p < 4; ++p) any = any || b->gexec[p] || b->graph[p] || b->multi_exec[p] || b->multi_graph[p];
+    b->graph_orders = -1;
+    if (!any) return;
+    std::lock_guard<std::mutex> one(graph_calls);
     for (int p = 0; p < 4; ++p) {
         if (b->gexec[p]) (void)hipGraphExecDestroy(b->gexec[p]);
         if (b->graph[p]) (void)hipGraphDestroy(b->graph[p]);
@@ -2127,7 +2142,6 @@ void drop_graph(swe_batch *b)
         b->gexec[p] = b->multi_exec[p] = nullptr;
         b->graph[p] = b->multi_graph[p] = nullptr;
     }
-    b->graph_orders = -1;
 }
 
 // Capacity of a pool that has to hold need elements: twice the current one
@@ -2347,6 +2361,7 @@ hipError_t enqueue_class_step(swe_batch *b, int p, Sink &k)
 // one chain.
 hipError_t build_class_graph(swe_batch *b, int p, int nsteps, hipGraph_t *g_out, hipGraphExec_t *x_out)
 {
+    std::lock_guard<std::mutex> one(graph_calls);
     hipGraph_t g = nullptr;
     hipError_t e = hipGraphCreate(&g, 0);
     if (e != hipSuccess) return e;

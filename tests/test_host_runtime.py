@@ -33,3 +33,52 @@ def test_read_back_without_host_memory_does_not_throw(lib):
                 assert st == swe.SWE_OK, st
             assert count("pinned allocations") == 1
     """)
+
+
+def test_step_graphs_are_built_and_destroyed_one_at_a_time_and_at_rest(lib):
+    """Contexts with static order maps (whose graphs have branches) in several
+    threads, beside a batch whose members come and go."""
+    host_runtime.run(lib, """
+        def contexts(seed):
+            for i in range(4):
+                prob = I.config_dambreak(n=12 + 2 * i, seed=seed)
+                with swe.context_for(prob, separate=1 + i % 2) as ctx:
+                    for shift in range(3):
+                        ctx.set_order(np.roll(prob.p, shift))
+                        ctx.step(20, 1e-5)
+                    ctx.sync()
+
+        def batch():
+            with swe.Batch(budget_bytes=64 << 20, max_instances=8) as b:
+                members = []
+                for i in range(12):
+                    p = 1 + i % 3
+                    m = swe.context_for(I.config_c2(n=10, p=p))
+                    members.append((b.admit(m, 100, 1.0), m))
+                    b.tick(17)
+                    if len(members) > 3:
+                        slot, m = members.pop(0)
+                        b.retire(slot)
+                        m.close()
+                for slot, m in members:
+                    b.retire(slot)
+                    m.close()
+
+        errors = []
+        def guarded(f, *a):
+            try:
+                f(*a)
+            except BaseException as e:
+                errors.append(e)
+
+        threads = [threading.Thread(target=guarded, args=(contexts, s)) for s in range(4)]
+        threads.append(threading.Thread(target=guarded, args=(batch,)))
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        assert not errors, errors
+        assert count("graphs built") > 20
+        assert count("graphs destroyed in flight") == 0
+        assert count("graph calls at once") == 1, count("graph calls at once")
+    """)
