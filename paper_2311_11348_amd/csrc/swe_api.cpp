@@ -19,6 +19,7 @@
 #include <mutex>
 #include <new>
 #include <sched.h>
+#include <shared_mutex>
 #include <string>
 #include <thread>
 #include <unordered_map>
@@ -119,6 +120,53 @@ swe_status fail(swe_ctx *c, swe_status s, const std::string &msg)
                         std::string(#expr) + ": " + hipGetErrorString(e_));                      \
     } while (0)
 
+// Step graphs are built and destroyed by one thread of the process at a time,
+// while no other is inside a runtime call that allocates, frees, or makes or
+// ends a stream, and destroyed only when their replays are over (every caller
+// has waited for the stream since the last one).  A served run in which branched
+// graphs were rebuilt beside other threads' calls ended in a fault of the host
+// whose cause is not known; a mesh with a static order map still has branches.
+std::shared_mutex graph_calls;
+typedef std::lock_guard<std::shared_mutex> GraphCall;
+typedef std::shared_lock<std::shared_mutex> OtherCall;
+
+template <typename T>
+hipError_t dev_alloc(T **p, size_t n)
+{
+    OtherCall l(graph_calls);
+    return hipMalloc(reinterpret_cast<void **>(p), n);
+}
+
+hipError_t dev_free(void *p)
+{
+    OtherCall l(graph_calls);
+    return hipFree(p);
+}
+
+hipError_t pinned_alloc(void **p, size_t n, unsigned flags)
+{
+    OtherCall l(graph_calls);
+    return hipHostMalloc(p, n, flags);
+}
+
+hipError_t pinned_free(void *p)
+{
+    OtherCall l(graph_calls);
+    return hipHostFree(p);
+}
+
+hipError_t stream_make(hipStream_t *s)
+{
+    OtherCall l(graph_calls);
+    return hipStreamCreateWithFlags(s, hipStreamNonBlocking);
+}
+
+hipError_t stream_end(hipStream_t s)
+{
+    OtherCall l(graph_calls);
+    return hipStreamDestroy(s);
+}
+
 // Every transfer of a context is ordered on its base stream (the library's
 // kernels run on non-blocking streams, which the null stream does not order
 // against); host-to-device copies wait until the data has left the host
@@ -138,17 +186,10 @@ hipError_t d2h(swe_ctx *c, void *dst, const void *src, size_t bytes)
 
 hipError_t dzero(swe_ctx *c, void *dst, size_t bytes) { return hipMemsetAsync(dst, 0, bytes, c->s_base); }
 
-// Step graphs are built and destroyed by one thread of the process at a time,
-// and destroyed only when their replays are over (every caller has waited for
-// the stream since the last one).  A served run in which branched graphs were
-// rebuilt beside other threads' calls ended in a fault of the host whose cause
-// is not known; a mesh with a static order map still has branches.
-std::mutex graph_calls;
-
 void drop_step_graph(swe_ctx *c)
 {
     if (!c->step_exec && !c->step_graph && !c->multi_exec && !c->multi_graph) return c->graph_key.clear();
-    std::lock_guard<std::mutex> one(graph_calls);
+    GraphCall one(graph_calls);
     if (c->step_exec) (void)hipGraphExecDestroy(c->step_exec);
     if (c->step_graph) (void)hipGraphDestroy(c->step_graph);
     if (c->multi_exec) (void)hipGraphExecDestroy(c->multi_exec);
@@ -160,7 +201,7 @@ void drop_step_graph(swe_ctx *c)
 
 void free_tiles(swe_ctx *c)
 {
-    if (c->d_tiles) (void)hipFree(c->d_tiles);
+    if (c->d_tiles) (void)dev_free(c->d_tiles);
     c->d_tiles = nullptr;
     c->tiles = TileView{};
 }
@@ -168,10 +209,10 @@ void free_tiles(swe_ctx *c)
 void free_mesh(swe_ctx *c)
 {
     drop_step_graph(c);
-    if (c->d_inst) (void)hipFree(c->d_inst);
+    if (c->d_inst) (void)dev_free(c->d_inst);
     c->d_inst = nullptr;
-    if (c->d_items) (void)hipFree(c->d_items);
-    if (c->d_item_off) (void)hipFree(c->d_item_off);
+    if (c->d_items) (void)dev_free(c->d_items);
+    if (c->d_item_off) (void)dev_free(c->d_item_off);
     c->d_items = nullptr;
     c->d_item_off = nullptr;
     free_tiles(c);
@@ -179,7 +220,7 @@ void free_mesh(swe_ctx *c)
                     c->d_U[0], c->d_U[1], c->d_L, c->d_src, c->d_flag, c->d_part, c->d_mass,
                     c->d_inlist, c->d_Lb, c->d_Lc, c->d_list, c->d_cnt, c->d_pnew, c->d_I};
     for (void *q : ptrs)
-        if (q) (void)hipFree(q);
+        if (q) (void)dev_free(q);
     c->d_vtx = nullptr; c->d_ev = nullptr; c->d_nb = nullptr; c->d_nbk = nullptr; c->d_p = nullptr; c->d_iperm = nullptr;
     c->d_C[0] = c->d_C[1] = c->d_U[0] = c->d_U[1] = nullptr;
     c->d_L = c->d_src = nullptr;
@@ -188,7 +229,7 @@ void free_mesh(swe_ctx *c)
     c->d_pnew = nullptr; c->d_I = nullptr;
     void *h[] = {c->h_C, c->h_U, c->h_Lc};
     for (void *q : h)
-        if (q) (void)hipHostFree(q);
+        if (q) (void)pinned_free(q);
     c->h_C = c->h_U = c->h_Lc = nullptr;
     c->h_vtx.clear();
     c->have_mesh = false;
@@ -203,7 +244,7 @@ void release_state_buffers(swe_ctx *c)
     drop_step_graph(c);
     void *q[] = {c->d_C[0], c->d_C[1], c->d_U[0], c->d_U[1], c->d_L, c->d_items, c->d_item_off};
     for (void *x : q)
-        if (x) (void)hipFree(x);
+        if (x) (void)dev_free(x);
     c->d_C[0] = c->d_C[1] = c->d_U[0] = c->d_U[1] = c->d_L = nullptr;
     c->d_items = nullptr;
     c->d_item_off = nullptr;
@@ -216,12 +257,12 @@ swe_status restore_state_buffers(swe_ctx *c)
     if (c->d_C[0]) return SWE_OK;
     const size_t w = c->rsz, K = c->K, S = c->stride;
     for (int b = 0; b < 2; ++b) {
-        HIP_TRY(c, hipMalloc(&c->d_C[b], w * 3 * K * S));
-        HIP_TRY(c, hipMalloc(&c->d_U[b], w * 2 * K * S));
+        HIP_TRY(c, dev_alloc(&c->d_C[b], w * 3 * K * S));
+        HIP_TRY(c, dev_alloc(&c->d_U[b], w * 2 * K * S));
         HIP_TRY(c, dzero(c, c->d_C[b], w * 3 * K * S));
         HIP_TRY(c, dzero(c, c->d_U[b], w * 2 * K * S));
     }
-    HIP_TRY(c, hipMalloc(&c->d_L, w * 3 * K * S));
+    HIP_TRY(c, dev_alloc(&c->d_L, w * 3 * K * S));
     HIP_TRY(c, hipStreamSynchronize(c->s_base));
     return SWE_OK;
 }
@@ -526,9 +567,9 @@ hipError_t host_mirrors(swe_ctx *c)
 {
     if (c->h_C) return hipSuccess;
     const size_t S = c->stride, K = c->K;
-    hipError_t e = hipHostMalloc(&c->h_C, sizeof(Real) * 3 * K * S, hipHostMallocDefault);
-    if (e == hipSuccess) e = hipHostMalloc(&c->h_U, sizeof(Real) * 2 * K * S, hipHostMallocDefault);
-    if (e == hipSuccess) e = hipHostMalloc(&c->h_Lc, sizeof(Real) * 3 * K * S, hipHostMallocDefault);
+    hipError_t e = pinned_alloc(&c->h_C, sizeof(Real) * 3 * K * S, hipHostMallocDefault);
+    if (e == hipSuccess) e = pinned_alloc(&c->h_U, sizeof(Real) * 2 * K * S, hipHostMallocDefault);
+    if (e == hipSuccess) e = pinned_alloc(&c->h_Lc, sizeof(Real) * 3 * K * S, hipHostMallocDefault);
     if (e != hipSuccess) return e;
     std::memset(c->h_C, 0, sizeof(Real) * 3 * K * S);
     std::memset(c->h_U, 0, sizeof(Real) * 2 * K * S);
@@ -720,7 +761,7 @@ constexpr int GRAPH_STEPS = 8;
 
 hipError_t build_graph(swe_ctx *c, int nsteps, hipGraph_t *g_out, hipGraphExec_t *x_out)
 {
-    std::lock_guard<std::mutex> one(graph_calls);
+    GraphCall one(graph_calls);
     hipGraph_t g = nullptr;
     hipError_t e = hipGraphCreate(&g, 0);
     if (e != hipSuccess) return e;
@@ -873,7 +914,7 @@ void ring_release()
     std::lock_guard<std::mutex> n(ring_count);
     if (--ring_owners > 0) return;
     std::lock_guard<std::mutex> u(ring_use);
-    if (ring_mem) (void)hipHostFree(ring_mem);
+    if (ring_mem) (void)pinned_free(ring_mem);
     ring_mem = nullptr;
 }
 
@@ -969,7 +1010,7 @@ swe_status download(swe_ctx *c, const void *src, int stride, int first, int ncom
         if (u.owns_lock()) {
             if (!ring_mem && sizeof(double) * n * (size_t)c->ne >= RING_FROM) {
                 void *q = nullptr;
-                if (hipHostMalloc(&q, RING_SLOTS * RING_SLOT, hipHostMallocPortable | hipHostMallocCoherent) == hipSuccess)
+                if (pinned_alloc(&q, RING_SLOTS * RING_SLOT, hipHostMallocPortable | hipHostMallocCoherent) == hipSuccess)
                     ring_mem = static_cast<char *>(q);
                 else
                     (void)hipGetLastError();
@@ -984,7 +1025,7 @@ swe_status download(swe_ctx *c, const void *src, int stride, int first, int ncom
     void *own = nullptr;
     if (!st) {
         bytes = sizeof(double) * n * (size_t)c->ne;
-        HIP_TRY(c, hipMalloc(&own, bytes));
+        HIP_TRY(c, dev_alloc(&own, bytes));
         st = own;
     }
     const int64_t part = stage_elements(bytes, n);
@@ -995,7 +1036,7 @@ swe_status download(swe_ctx *c, const void *src, int stride, int first, int ncom
                         static_cast<double *>(st), c->s_base);
         if (e == hipSuccess) e = d2h(c, out + (size_t)u0 * n, st, sizeof(double) * n * (size_t)(u1 - u0));
     }
-    if (own) (void)hipFree(own);
+    if (own) (void)dev_free(own);
     HIP_TRY(c, e);
     return SWE_OK;
 }
@@ -1100,7 +1141,7 @@ swe_status build_tiles(swe_ctx *c)
     const int start = fill >= 192 ? 192 : std::max(96, (int)(fill + 7) / 8 * 8), least = fill > 192 ? 128 : 64;
     for (int len = start; len >= least && one_launch_pays(c, len);) {
         const size_t nt = (size_t)((c->ne + len - 1) / len);
-        if (hipMalloc(&c->d_tiles, nt * TILE_BYTES) != hipSuccess) {
+        if (dev_alloc(&c->d_tiles, nt * TILE_BYTES) != hipSuccess) {
             // no room for them: the mesh keeps two launches per step
             (void)hipGetLastError();
             c->d_tiles = nullptr;
@@ -1138,8 +1179,8 @@ swe_status build_tiles(swe_ctx *c)
 swe_status build_items(swe_ctx *c)
 {
     if (swe_status st = build_tiles(c)) return st;
-    if (c->d_items) (void)hipFree(c->d_items);
-    if (c->d_item_off) (void)hipFree(c->d_item_off);
+    if (c->d_items) (void)dev_free(c->d_items);
+    if (c->d_item_off) (void)dev_free(c->d_item_off);
     c->d_items = nullptr;
     c->d_item_off = nullptr;
     c->item_blocks = 0;
@@ -1215,8 +1256,8 @@ swe_status build_items(swe_ctx *c)
             for (int64_t bi = cover + 1; bi <= nblk; ++bi) ioff[(size_t)bi] = (int)items.size();
         }
         if (cover > 0) {
-            HIP_TRY(c, hipMalloc(&c->d_items, sizeof(unsigned) * std::max<size_t>(items.size(), 1)));
-            HIP_TRY(c, hipMalloc(&c->d_item_off, sizeof(int) * ioff.size()));
+            HIP_TRY(c, dev_alloc(&c->d_items, sizeof(unsigned) * std::max<size_t>(items.size(), 1)));
+            HIP_TRY(c, dev_alloc(&c->d_item_off, sizeof(int) * ioff.size()));
             if (!items.empty()) HIP_TRY(c, h2d(c, c->d_items, items.data(), sizeof(unsigned) * items.size()));
             HIP_TRY(c, h2d(c, c->d_item_off, ioff.data(), sizeof(int) * ioff.size()));
             c->item_blocks = cover;
@@ -1419,7 +1460,7 @@ swe_status swe_create(const swe_config *cfg, swe_ctx **out)
     if (cfg->stream_base) {
         c->s_base = static_cast<hipStream_t>(cfg->stream_base);
     } else {
-        if (hipStreamCreateWithFlags(&c->s_base, hipStreamNonBlocking) != hipSuccess) {
+        if (stream_make(&c->s_base) != hipSuccess) {
             delete c;
             return SWE_EDEVICE;
         }
@@ -1428,8 +1469,8 @@ swe_status swe_create(const swe_config *cfg, swe_ctx **out)
     if (cfg->stream_corr) {
         c->s_corr = static_cast<hipStream_t>(cfg->stream_corr);
     } else {
-        if (hipStreamCreateWithFlags(&c->s_corr, hipStreamNonBlocking) != hipSuccess) {
-            if (c->own_base) (void)hipStreamDestroy(c->s_base);
+        if (stream_make(&c->s_corr) != hipSuccess) {
+            if (c->own_base) (void)stream_end(c->s_base);
             delete c;
             return SWE_EDEVICE;
         }
@@ -1437,8 +1478,8 @@ swe_status swe_create(const swe_config *cfg, swe_ctx **out)
     }
     if (hipEventCreateWithFlags(&c->ev_ready, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&c->ev_corr, hipEventDisableTiming) != hipSuccess) {
-        if (c->own_base) (void)hipStreamDestroy(c->s_base);
-        if (c->own_corr) (void)hipStreamDestroy(c->s_corr);
+        if (c->own_base) (void)stream_end(c->s_base);
+        if (c->own_corr) (void)stream_end(c->s_corr);
         delete c;
         return SWE_EDEVICE;
     }
@@ -1455,8 +1496,8 @@ void swe_destroy(swe_ctx *c)
     free_mesh(c);
     if (c->ev_ready) (void)hipEventDestroy(c->ev_ready);
     if (c->ev_corr) (void)hipEventDestroy(c->ev_corr);
-    if (c->own_base) (void)hipStreamDestroy(c->s_base);
-    if (c->own_corr) (void)hipStreamDestroy(c->s_corr);
+    if (c->own_base) (void)stream_end(c->s_base);
+    if (c->own_corr) (void)stream_end(c->s_corr);
     delete c;
     ring_release();
 }
@@ -1597,24 +1638,24 @@ swe_status swe_set_mesh(swe_ctx *c, int64_t nv, const double *vxy, int64_t ne, c
             }
     // device buffers
     const size_t w = c->rsz, K = c->K;
-    HIP_TRY(c, hipMalloc(&c->d_vtx, sizeof(double4) * nv));
-    HIP_TRY(c, hipMalloc(&c->d_ev, sizeof(int) * 3 * S));
-    HIP_TRY(c, hipMalloc(&c->d_nb, sizeof(int) * 3 * S));
-    HIP_TRY(c, hipMalloc(&c->d_nbk, S));
-    HIP_TRY(c, hipMalloc(&c->d_p, S));
-    HIP_TRY(c, hipMalloc(&c->d_iperm, sizeof(int) * S));
+    HIP_TRY(c, dev_alloc(&c->d_vtx, sizeof(double4) * nv));
+    HIP_TRY(c, dev_alloc(&c->d_ev, sizeof(int) * 3 * S));
+    HIP_TRY(c, dev_alloc(&c->d_nb, sizeof(int) * 3 * S));
+    HIP_TRY(c, dev_alloc(&c->d_nbk, S));
+    HIP_TRY(c, dev_alloc(&c->d_p, S));
+    HIP_TRY(c, dev_alloc(&c->d_iperm, sizeof(int) * S));
     for (int b = 0; b < 2; ++b) {
-        HIP_TRY(c, hipMalloc(&c->d_C[b], w * 3 * K * S));
-        HIP_TRY(c, hipMalloc(&c->d_U[b], w * 2 * K * S));
+        HIP_TRY(c, dev_alloc(&c->d_C[b], w * 3 * K * S));
+        HIP_TRY(c, dev_alloc(&c->d_U[b], w * 2 * K * S));
         HIP_TRY(c, dzero(c, c->d_C[b], w * 3 * K * S));
         HIP_TRY(c, dzero(c, c->d_U[b], w * 2 * K * S));
     }
-    HIP_TRY(c, hipMalloc(&c->d_L, w * 3 * K * S));
-    HIP_TRY(c, hipMalloc(&c->d_flag, 3 * sizeof(int)));   // failure flag; two words for transfers and set-up
-    HIP_TRY(c, hipMalloc(&c->d_inst, 2 * sizeof(InstDesc)));
+    HIP_TRY(c, dev_alloc(&c->d_L, w * 3 * K * S));
+    HIP_TRY(c, dev_alloc(&c->d_flag, 3 * sizeof(int)));   // failure flag; two words for transfers and set-up
+    HIP_TRY(c, dev_alloc(&c->d_inst, 2 * sizeof(InstDesc)));
     HIP_TRY(c, dzero(c, c->d_flag, sizeof(int)));
-    HIP_TRY(c, hipMalloc(&c->d_part, sizeof(double) * (mass_partials((int)ne) + 1)));
-    HIP_TRY(c, hipMalloc(&c->d_mass, sizeof(double)));
+    HIP_TRY(c, dev_alloc(&c->d_part, sizeof(double) * (mass_partials((int)ne) + 1)));
+    HIP_TRY(c, dev_alloc(&c->d_mass, sizeof(double)));
     HIP_TRY(c, h2d(c, c->d_ev, c->ev.data(), sizeof(int) * 3 * S));
     HIP_TRY(c, h2d(c, c->d_nb, nb.data(), sizeof(int) * 3 * S));
     HIP_TRY(c, h2d(c, c->d_nbk, nbk.data(), S));
@@ -1628,15 +1669,15 @@ swe_status swe_set_mesh(swe_ctx *c, int64_t nv, const double *vxy, int64_t ne, c
     if (st0) return st0;
     if (separated(c) || c->cfg.adapt) {
         const int KB = K_OF[c->cfg.p_base];
-        HIP_TRY(c, hipMalloc(&c->d_inlist, S));
+        HIP_TRY(c, dev_alloc(&c->d_inlist, S));
         HIP_TRY(c, dzero(c, c->d_inlist, S));
-        HIP_TRY(c, hipMalloc(&c->d_Lb, w * 3 * KB * S));
-        HIP_TRY(c, hipMalloc(&c->d_Lc, w * 3 * K * S));
-        HIP_TRY(c, hipMalloc(&c->d_list, sizeof(int) * 4 * (size_t)ne));
-        HIP_TRY(c, hipMalloc(&c->d_cnt, sizeof(int) * 4));
+        HIP_TRY(c, dev_alloc(&c->d_Lb, w * 3 * KB * S));
+        HIP_TRY(c, dev_alloc(&c->d_Lc, w * 3 * K * S));
+        HIP_TRY(c, dev_alloc(&c->d_list, sizeof(int) * 4 * (size_t)ne));
+        HIP_TRY(c, dev_alloc(&c->d_cnt, sizeof(int) * 4));
         HIP_TRY(c, dzero(c, c->d_cnt, sizeof(int) * 4));
-        HIP_TRY(c, hipMalloc(&c->d_pnew, S));
-        HIP_TRY(c, hipMalloc(&c->d_I, sizeof(double) * S));
+        HIP_TRY(c, dev_alloc(&c->d_pnew, S));
+        HIP_TRY(c, dev_alloc(&c->d_I, sizeof(double) * S));
     }
     c->p.assign(ne, (signed char)(separated(c) ? c->cfg.p_base : c->cfg.p_max));
     swe_status st = upload_order(c);
@@ -1785,7 +1826,7 @@ swe_status swe_set_source(swe_ctx *c, const double *coef)
     if (!c->have_mesh) return fail(c, SWE_EINVAL, "set_mesh first");
     HIP_TRY(c, hipStreamSynchronize(c->s_base));
     if (!coef) {
-        if (c->d_src) (void)hipFree(c->d_src);
+        if (c->d_src) (void)dev_free(c->d_src);
         c->d_src = nullptr;
         return SWE_OK;
     }
@@ -1794,7 +1835,7 @@ swe_status swe_set_source(swe_ctx *c, const double *coef)
     const size_t bytes = c->rsz * 3 * c->K * c->stride;
     swe_status st = upload_state(c, coef, c->d_C[1]);
     if (st) return st;
-    if (!c->d_src) HIP_TRY(c, hipMalloc(&c->d_src, bytes));
+    if (!c->d_src) HIP_TRY(c, dev_alloc(&c->d_src, bytes));
     HIP_TRY(c, hipMemcpyAsync(c->d_src, c->d_C[1], bytes, hipMemcpyDeviceToDevice, c->s_base));
     HIP_TRY(c, dzero(c, c->d_C[1], bytes));
     HIP_TRY(c, hipStreamSynchronize(c->s_base));
@@ -2133,7 +2174,7 @@ void drop_graph(swe_batch *b)
     for (int p = 0; p < 4; ++p) any = any || b->gexec[p] || b->graph[p] || b->multi_exec[p] || b->multi_graph[p];
     b->graph_orders = -1;
     if (!any) return;
-    std::lock_guard<std::mutex> one(graph_calls);
+    GraphCall one(graph_calls);
     for (int p = 0; p < 4; ++p) {
         if (b->gexec[p]) (void)hipGraphExecDestroy(b->gexec[p]);
         if (b->graph[p]) (void)hipGraphDestroy(b->graph[p]);
@@ -2166,18 +2207,18 @@ swe_status grow_pool(swe_batch *b, int p, int64_t nc)
         return bfail(b, SWE_EUNSUPPORTED, "pool of one order would exceed 2 GiB per array");
     PoolView v{};
     v.cap = (int)nc;
-    BHIP_TRY(b, hipMalloc(&v.C0, b->w * 3 * K * nc));
-    BHIP_TRY(b, hipMalloc(&v.C1, b->w * 3 * K * nc));
-    BHIP_TRY(b, hipMalloc(&v.U0, b->w * 2 * K * nc));
-    BHIP_TRY(b, hipMalloc(&v.U1, b->w * 2 * K * nc));
-    BHIP_TRY(b, hipMalloc(&v.ev, sizeof(int) * 3 * nc));
-    BHIP_TRY(b, hipMalloc(&v.nb, sizeof(int) * 3 * nc));
-    BHIP_TRY(b, hipMalloc(&v.nbk, nc));
-    BHIP_TRY(b, hipMalloc(&v.ep, nc));
-    BHIP_TRY(b, hipMalloc(&v.pnew, nc));
+    BHIP_TRY(b, dev_alloc(&v.C0, b->w * 3 * K * nc));
+    BHIP_TRY(b, dev_alloc(&v.C1, b->w * 3 * K * nc));
+    BHIP_TRY(b, dev_alloc(&v.U0, b->w * 2 * K * nc));
+    BHIP_TRY(b, dev_alloc(&v.U1, b->w * 2 * K * nc));
+    BHIP_TRY(b, dev_alloc(&v.ev, sizeof(int) * 3 * nc));
+    BHIP_TRY(b, dev_alloc(&v.nb, sizeof(int) * 3 * nc));
+    BHIP_TRY(b, dev_alloc(&v.nbk, nc));
+    BHIP_TRY(b, dev_alloc(&v.ep, nc));
+    BHIP_TRY(b, dev_alloc(&v.pnew, nc));
     if (stage_sh_supported(p, b->fp32)) {
-        BHIP_TRY(b, hipMalloc(&v.items, sizeof(unsigned) * 3 * nc));
-        BHIP_TRY(b, hipMalloc(&v.nitems, sizeof(int) * (nc / BLOCK)));
+        BHIP_TRY(b, dev_alloc(&v.items, sizeof(unsigned) * 3 * nc));
+        BHIP_TRY(b, dev_alloc(&v.nitems, sizeof(int) * (nc / BLOCK)));
         BHIP_TRY(b, hipMemsetAsync(v.nitems, 0, sizeof(int) * (nc / BLOCK), b->s));
     }
     BHIP_TRY(b, hipMemsetAsync(v.C1, 0, b->w * 3 * K * nc, b->s));
@@ -2197,7 +2238,7 @@ swe_status grow_pool(swe_batch *b, int p, int64_t nc)
         BHIP_TRY(b, hipStreamSynchronize(b->s));
         void *old[] = {P.v.C0, P.v.C1, P.v.U0, P.v.U1, P.v.ev, P.v.nb, P.v.nbk, P.v.ep, P.v.pnew, P.v.items,
                        P.v.nitems};
-        for (void *q : old) (void)hipFree(q);
+        for (void *q : old) (void)dev_free(q);
     }
     b->alloc += pool_bytes(p, b->fp32, nc) - pool_bytes(p, b->fp32, oc);
     P.v = v;
@@ -2205,14 +2246,14 @@ swe_status grow_pool(swe_batch *b, int p, int64_t nc)
     // tile list capacity follows the pool: at most one tile per 64 elements
     const int tc = (int)(nc / 64 + 1);
     int2 *nt = nullptr;
-    BHIP_TRY(b, hipMalloc(&nt, sizeof(int2) * tc));
-    if (b->d_tiles[p]) (void)hipFree(b->d_tiles[p]);
+    BHIP_TRY(b, dev_alloc(&nt, sizeof(int2) * tc));
+    if (b->d_tiles[p]) (void)dev_free(b->d_tiles[p]);
     b->d_tiles[p] = nt;
     b->tile_cap[p] = tc;
     const int ac = (int)(nc / BLOCK + 1);
     int2 *na = nullptr;
-    BHIP_TRY(b, hipMalloc(&na, sizeof(int2) * ac));
-    if (b->d_atiles[p]) (void)hipFree(b->d_atiles[p]);
+    BHIP_TRY(b, dev_alloc(&na, sizeof(int2) * ac));
+    if (b->d_atiles[p]) (void)dev_free(b->d_atiles[p]);
     b->d_atiles[p] = na;
     b->atile_cap[p] = ac;
     drop_graph(b);
@@ -2224,11 +2265,11 @@ swe_status grow_vertices(swe_batch *b, int64_t nc)
 {
     if (nc <= b->vra.cap) return SWE_OK;
     double4 *v = nullptr;
-    BHIP_TRY(b, hipMalloc(&v, sizeof(double4) * nc));
+    BHIP_TRY(b, dev_alloc(&v, sizeof(double4) * nc));
     if (b->vra.cap) {
         BHIP_TRY(b, hipMemcpyAsync(v, b->d_vtx, sizeof(double4) * b->vra.cap, hipMemcpyDeviceToDevice, b->s));
         BHIP_TRY(b, hipStreamSynchronize(b->s));
-        (void)hipFree(b->d_vtx);
+        (void)dev_free(b->d_vtx);
     }
     b->alloc += (int64_t)sizeof(double4) * (nc - b->vra.cap);
     b->d_vtx = v;
@@ -2245,7 +2286,7 @@ void release_pool(swe_batch *b, int p)
     void *q[] = {P.v.C0, P.v.C1, P.v.U0, P.v.U1, P.v.ev, P.v.nb, P.v.nbk, P.v.ep, P.v.pnew, P.v.items, P.v.nitems,
                  b->d_tiles[p], b->d_atiles[p]};
     for (void *x : q)
-        if (x) (void)hipFree(x);
+        if (x) (void)dev_free(x);
     b->alloc -= pool_bytes(p, b->fp32, P.ra.cap);
     P.v = PoolView{};
     P.ra.clear();
@@ -2259,7 +2300,7 @@ void release_pool(swe_batch *b, int p)
 void release_vertices(swe_batch *b)
 {
     if (b->vra.cap == 0) return;
-    (void)hipFree(b->d_vtx);
+    (void)dev_free(b->d_vtx);
     b->alloc -= (int64_t)sizeof(double4) * b->vra.cap;
     b->d_vtx = nullptr;
     b->vra.clear();
@@ -2361,7 +2402,7 @@ hipError_t enqueue_class_step(swe_batch *b, int p, Sink &k)
 // one chain.
 hipError_t build_class_graph(swe_batch *b, int p, int nsteps, hipGraph_t *g_out, hipGraphExec_t *x_out)
 {
-    std::lock_guard<std::mutex> one(graph_calls);
+    GraphCall one(graph_calls);
     hipGraph_t g = nullptr;
     hipError_t e = hipGraphCreate(&g, 0);
     if (e != hipSuccess) return e;
@@ -2405,7 +2446,7 @@ hipStream_t fork_class(swe_batch *b, int n)
     const int i = n - 1;
     bool ok = b->fork || hipEventCreateWithFlags(&b->fork, hipEventDisableTiming) == hipSuccess;
     ok = ok && (b->join[i] || hipEventCreateWithFlags(&b->join[i], hipEventDisableTiming) == hipSuccess);
-    ok = ok && (b->class_s[i] || hipStreamCreateWithFlags(&b->class_s[i], hipStreamNonBlocking) == hipSuccess);
+    ok = ok && (b->class_s[i] || stream_make(&b->class_s[i]) == hipSuccess);
     ok = ok && hipEventRecord(b->fork, b->s) == hipSuccess;
     ok = ok && hipStreamWaitEvent(b->class_s[i], b->fork, 0) == hipSuccess;
     if (ok) return b->class_s[i];
@@ -2494,16 +2535,16 @@ swe_status swe_batch_create(const swe_config *cfg, int64_t budget, int max_insta
         b->ncu = prop.multiProcessorCount;
     if (cfg->stream_base) {
         b->s = static_cast<hipStream_t>(cfg->stream_base);
-    } else if (hipStreamCreateWithFlags(&b->s, hipStreamNonBlocking) != hipSuccess) {
+    } else if (stream_make(&b->s) != hipSuccess) {
         delete b;
         return SWE_EDEVICE;
     } else {
         b->own_s = true;
     }
-    if (hipMalloc(&b->d_inst, sizeof(InstDesc) * max_instances) != hipSuccess ||
-        hipMalloc(&b->d_flags, sizeof(int) * max_instances) != hipSuccess ||
-        hipMalloc(&b->d_ntiles, sizeof(int) * 4) != hipSuccess ||
-        hipMalloc(&b->d_natiles, sizeof(int) * 4) != hipSuccess) {
+    if (dev_alloc(&b->d_inst, sizeof(InstDesc) * max_instances) != hipSuccess ||
+        dev_alloc(&b->d_flags, sizeof(int) * max_instances) != hipSuccess ||
+        dev_alloc(&b->d_ntiles, sizeof(int) * 4) != hipSuccess ||
+        dev_alloc(&b->d_natiles, sizeof(int) * 4) != hipSuccess) {
         swe_batch_destroy(b);
         return SWE_ENOMEM;
     }
@@ -2544,13 +2585,13 @@ void swe_batch_destroy(swe_batch *b)
             ptrs.push_back(q);
     }
     for (void *q : ptrs)
-        if (q) (void)hipFree(q);
+        if (q) (void)dev_free(q);
     if (b->fork) (void)hipEventDestroy(b->fork);
     for (int i = 0; i < 3; ++i) {
         if (b->join[i]) (void)hipEventDestroy(b->join[i]);
-        if (b->class_s[i]) (void)hipStreamDestroy(b->class_s[i]);
+        if (b->class_s[i]) (void)stream_end(b->class_s[i]);
     }
-    if (b->own_s) (void)hipStreamDestroy(b->s);
+    if (b->own_s) (void)stream_end(b->s);
     delete b;
 }
 

@@ -64,8 +64,25 @@ struct GraphCall {
     }
 };
 
+// an allocation, a free, a stream made or ended: whether a graph is being built or destroyed meanwhile
+struct OtherCall {
+    OtherCall() { look(); }
+    ~OtherCall()
+    {
+        usleep(20);
+        look();
+    }
+    static void look()
+    {
+        if (in_graph_call.load() == 0) return;
+        Model l;
+        counts["other calls beside graph calls"] += 1;
+    }
+};
+
 hipError_t alloc(void **p, size_t n)
 {
+    OtherCall call;
     *p = calloc(1, n ? n : 1);
     Model l;
     sizes[*p] = n;
@@ -76,6 +93,7 @@ hipError_t alloc(void **p, size_t n)
 
 hipError_t release(void *p)
 {
+    OtherCall call;
     {
         Model l;
         counts["bytes"] -= (long)sizes[p];
@@ -117,6 +135,7 @@ hipError_t hipMalloc(void **p, size_t n) { return alloc(p, n); }
 hipError_t hipFree(void *p) { return release(p); }
 hipError_t hipHostMalloc(void **p, size_t n, unsigned flags)
 {
+    OtherCall call;
     Model l;
     counts["pinned allocations"] += 1;
     if (!(flags & hipHostMallocCoherent)) counts["pinned allocations not coherent"] += 1;
@@ -125,6 +144,7 @@ hipError_t hipHostMalloc(void **p, size_t n, unsigned flags)
 }
 hipError_t hipHostFree(void *p)
 {
+    OtherCall call;
     free(p);
     return hipSuccess;
 }
@@ -143,9 +163,14 @@ hipError_t hipMemsetAsync(void *d, int v, size_t n, hipStream_t)
     memset(d, v, n);
     return hipSuccess;
 }
-hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { return handle(s); }
+hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned)
+{
+    OtherCall call;
+    return handle(s);
+}
 hipError_t hipStreamDestroy(hipStream_t s)
 {
+    OtherCall call;
     free(s);
     return hipSuccess;
 }

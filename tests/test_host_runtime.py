@@ -81,4 +81,5 @@ def test_step_graphs_are_built_and_destroyed_one_at_a_time_and_at_rest(lib):
         assert count("graphs built") > 20
         assert count("graphs destroyed in flight") == 0
         assert count("graph calls at once") == 1, count("graph calls at once")
+        assert count("other calls beside graph calls") == 0, count("other calls beside graph calls")
     """)
