@@ -171,7 +171,9 @@ swe_status swe_set_source(swe_ctx *ctx, const double *coef);
  * or eight steps are a graph of kernel nodes (base and correction branches
  * joined where the scheme joins them), replayed until nsteps are enqueued;
  * stage times and the open-sea elevation are computed on the device from
- * t0 + k dt. */
+ * t0 + k dt.  The first call of two or more steps that can take one launch per
+ * step prepares for it: it allocates and waits for the stream, unless the
+ * stream is being captured (that call's steps then take two launches each). */
 swe_status swe_step(swe_ctx *ctx, int64_t nsteps, double dt);
 
 /* Wait for queued work; returns SWE_ESTATE if a stage produced a non-finite

@@ -97,6 +97,7 @@ struct swe_ctx {
     int64_t item_blocks = 0;              // the leading blocks whose items are built
     void *d_tiles = nullptr;              // tile data of the one-launch step (one allocation)
     TileView tiles{};                     // its arrays; len 0: none
+    bool tiles_tried = false;             // built, or found not to fit or not to pay, for this numbering
     InstDesc *d_inst = nullptr;
     hipGraph_t step_graph = nullptr, multi_graph = nullptr;   // one step; GRAPH_STEPS steps
     hipGraphExec_t step_exec = nullptr, multi_exec = nullptr;
@@ -204,6 +205,7 @@ void free_tiles(swe_ctx *c)
     if (c->d_tiles) (void)dev_free(c->d_tiles);
     c->d_tiles = nullptr;
     c->tiles = TileView{};
+    c->tiles_tried = false;
 }
 
 void free_mesh(swe_ctx *c)
@@ -236,8 +238,8 @@ void free_mesh(swe_ctx *c)
 }
 
 // A batch member's state buffers (C0, C1, U0, U1, the right-hand-side
-// scratch, edge items, tiles) are released while it is resident: its state lives in
-// the batch's pool.  They are re-created (zero-filled) when the state comes
+// scratch, edge items, tiles) are released while it is resident: its state
+// lives in the batch's pool.  They are re-created (zero-filled) when the state comes
 // back; the edge items when the member leaves the batch.
 void release_state_buffers(swe_ctx *c)
 {
@@ -428,10 +430,13 @@ bool separated(const swe_ctx *c) { return c->cfg.separate && c->cfg.p_base < c->
 // with nothing between the stages.  A call's steps run in pairs (state buffer
 // 0 -> 1 -> 0), so the state rests in buffer 0 as ever; the last of an odd
 // number takes two stage launches.
-bool one_launch_steps(const swe_ctx *c)
+bool may_step_in_one(const swe_ctx *c)
 {
-    return c->tiles.len > 0 && c->uniform && !separated(c) && !c->cfg.adapt && !(c->cfg.h_min > 0.0);
+    return c->uniform && !separated(c) && !c->cfg.adapt && !(c->cfg.h_min > 0.0) &&
+           stage_sh_supported(c->cfg.p_max, c->fp32);
 }
+
+bool one_launch_steps(const swe_ctx *c) { return c->tiles.len > 0 && may_step_in_one(c); }
 
 template <typename Real>
 hipError_t enqueue_one_launch_step(Lanes &L, int in, double tn, double dt)
@@ -752,6 +757,7 @@ hipError_t enqueue_step_of(Lanes &L, int64_t s, int64_t paired, double tn, doubl
 std::vector<long long> step_graph_key(const swe_ctx *c)
 {
     return {(long long)(intptr_t)c->d_C[0], (long long)(intptr_t)c->d_src, c->uniform ? 1 : 0,
+            (long long)(intptr_t)c->d_tiles, c->tiles.len,
             c->list_cnt[0], c->list_cnt[1], c->list_cnt[2], c->list_cnt[3]};
 }
 
@@ -1122,8 +1128,7 @@ bool one_launch_pays(const swe_ctx *c, int len)
     return per_cu == 1 ? 5 * rt < 7 * rb : 2 * rt <= 3 * rb;
 }
 
-// Tiles of the one-launch step for the current numbering (replacing any built
-// before), by a device kernel: 192 owned elements each (three waves, the ring
+// Tiles of the one-launch step for the current numbering, by a device kernel: 192 owned elements each (three waves, the ring
 // in the fourth), or fewer, by eights, where some tile of the mesh is beyond a
 // block (a ring above 64 elements, many boundary edges); below 128 owned
 // elements the ring costs as much as they do, and the mesh keeps two launches
@@ -1135,8 +1140,6 @@ bool one_launch_pays(const swe_ctx *c, int len)
 // more, and their outside neighbours outnumber them).
 swe_status build_tiles(swe_ctx *c)
 {
-    free_tiles(c);
-    if (separated(c) || c->cfg.adapt || c->cfg.h_min > 0.0 || !stage_sh_supported(c->cfg.p_max, c->fp32)) return SWE_OK;
     const int64_t fill = (c->ne + c->ncu - 1) / c->ncu;   // elements per CU
     const int start = fill >= 192 ? 192 : std::max(96, (int)(fill + 7) / 8 * 8), least = fill > 192 ? 128 : 64;
     for (int len = start; len >= least && one_launch_pays(c, len);) {
@@ -1167,6 +1170,31 @@ swe_status build_tiles(swe_ctx *c)
     return SWE_OK;
 }
 
+// While one is alive, this thread's allocations are no concern of a stream
+// capture that another thread has under way.
+struct OwnCaptureRules {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    OwnCaptureRules() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~OwnCaptureRules() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
+// Tiles for a call of nsteps steps: built by the first call that can use them,
+// so that a context which only goes through a batch has none.  Building waits
+// for the stream; while it is being captured the steps take two launches.
+swe_status ready_tiles(swe_ctx *c, int64_t nsteps)
+{
+    if (c->tiles_tried || nsteps < 2 || !may_step_in_one(c)) return SWE_OK;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->s_base, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return SWE_OK;
+    }
+    OwnCaptureRules rules;
+    const swe_status st = build_tiles(c);
+    c->tiles_tried = true;
+    return st;
+}
+
 #ifndef SWE_SHARED_FLUX
 #define SWE_SHARED_FLUX 1
 #endif
@@ -1178,7 +1206,7 @@ swe_status build_tiles(swe_ctx *c)
 // blocks hold many edges to outside); else none.
 swe_status build_items(swe_ctx *c)
 {
-    if (swe_status st = build_tiles(c)) return st;
+    free_tiles(c);   // of another numbering
     if (c->d_items) (void)dev_free(c->d_items);
     if (c->d_item_off) (void)dev_free(c->d_item_off);
     c->d_items = nullptr;
@@ -1855,9 +1883,10 @@ swe_status swe_step(swe_ctx *c, int64_t nsteps, double dt)
     if (c->cfg.adapt) c->uniform = false;   // orders may differ from the first order update on
     if (c->cfg.hetero && (!c->grouped || c->d_src))
         return fail(c, SWE_EINVAL, "heterogeneous stages need a static order map (swe_set_order) and no extra source");
+    if (swe_status st = ready_tiles(c, nsteps)) return st;
     // graphs pay off where a step has many dependent kernels (order-separated
-    // and order-partitioned steps); a fused step is two plain launches; a
-    // heterogeneous stage waits for the host in the middle: launches
+    // and order-partitioned steps); a fused step is one or two plain launches;
+    // a heterogeneous stage waits for the host in the middle: launches
     const bool graph = c->ncon <= 4 && !c->cfg.hetero &&
                        (c->cfg.step_graph == 2 || (c->cfg.step_graph == 1 && separated(c)));
     if (graph) {

@@ -83,3 +83,26 @@ def test_step_graphs_are_built_and_destroyed_one_at_a_time_and_at_rest(lib):
         assert count("graph calls at once") == 1, count("graph calls at once")
         assert count("other calls beside graph calls") == 0, count("other calls beside graph calls")
     """)
+
+
+def test_tiles_are_built_by_the_call_that_uses_them(lib):
+    """Not for a context that only goes through a batch, nor when it comes back
+    from one; by the first call of several steps, once."""
+    host_runtime.run(lib, """
+        prob = I.config_c2(n=40, p=2)
+        with swe.Batch(budget_bytes=64 << 20, max_instances=8) as b, swe.context_for(prob) as ctx:
+            ctx.set_state(np.zeros((ctx.ne, 3, ctx.K)))
+            slot = b.admit(ctx, 50, 1.0)
+            b.tick(50)
+            b.retire(slot)
+            assert count("tile builds") == 0
+            ctx.step(1, 1.0)
+            assert count("tile builds") == 0
+            ctx.step(5, 1.0)
+            ctx.step(4, 1.0)
+            assert count("tile builds") == 1 and count("one-launch steps") == 8
+            slot = b.admit(ctx, 50, 1.0)
+            b.retire(slot)
+            ctx.step(2, 1.0)
+            assert count("tile builds") == 2 and count("one-launch steps") == 10
+    """)
