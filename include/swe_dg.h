@@ -223,9 +223,11 @@ const char *swe_last_error(const swe_ctx *ctx);
 /* Upper bound of the device bytes a batch-ready context (uniform order
  * p_max, not separated, not adaptive) with ne elements holds on its own
  * after swe_set_mesh (state, velocity, geometry, order map, scratch, edge
- * items, tiles of the one-launch step), and of what it takes resident in an
- * empty batch (its share of the pools plus the arrays it keeps); the vertex
- * count is bounded by that of a triangulated polygon with a few holes. */
+ * items), and of what it takes resident in an empty batch (its share of the
+ * pools plus the arrays it keeps); the vertex count is bounded by that of a
+ * triangulated polygon with a few holes.  A context that steps on its own adds
+ * what its first swe_step allocates: at most 76 bytes per element for the
+ * one-launch step. */
 int64_t swe_footprint_bytes(int64_t ne, int p_max, int precision);
 
 /* Free everything the context holds; NULL is accepted. */
@@ -255,7 +257,7 @@ void swe_destroy(swe_ctx *ctx);
  * batch holds: its per-order pools (capacity doubling while the budget
  * allows, exact growth otherwise; old and new arrays are counted together
  * while a pool grows), tile lists, vertex pool, and the arrays a member
- * keeps while resident (vertex and neighbour ids, vertices, flag).  A
+ * keeps while resident (vertex ids, neighbour edges, vertices, flags).  A
  * member's state buffers are released at admission (the pool holds its
  * state) and re-created when it is retired; swe_mass of a resident member
  * re-creates them for the call only, swe_get_state reads the pool.  A pool

@@ -238,16 +238,19 @@ void free_mesh(swe_ctx *c)
 }
 
 // A batch member's state buffers (C0, C1, U0, U1, the right-hand-side
-// scratch, edge items, tiles) are released while it is resident: its state
-// lives in the batch's pool.  They are re-created (zero-filled) when the state comes
-// back; the edge items when the member leaves the batch.
+// scratch, edge items, tiles, neighbour ids, clock) are released while it is
+// resident: its state lives in the batch's pool.  They are re-created
+// (zero-filled) when the state comes back; neighbour ids and edge items when
+// the member leaves the batch, tiles and clock when a step needs them.
 void release_state_buffers(swe_ctx *c)
 {
     drop_step_graph(c);
-    void *q[] = {c->d_C[0], c->d_C[1], c->d_U[0], c->d_U[1], c->d_L, c->d_items, c->d_item_off};
+    void *q[] = {c->d_C[0], c->d_C[1], c->d_U[0], c->d_U[1], c->d_L, c->d_items, c->d_item_off, c->d_nb, c->d_inst};
     for (void *x : q)
         if (x) (void)dev_free(x);
     c->d_C[0] = c->d_C[1] = c->d_U[0] = c->d_U[1] = c->d_L = nullptr;
+    c->d_nb = nullptr;
+    c->d_inst = nullptr;
     c->d_items = nullptr;
     c->d_item_off = nullptr;
     c->item_blocks = 0;
@@ -266,6 +269,16 @@ swe_status restore_state_buffers(swe_ctx *c)
     }
     HIP_TRY(c, dev_alloc(&c->d_L, w * 3 * K * S));
     HIP_TRY(c, hipStreamSynchronize(c->s_base));
+    return SWE_OK;
+}
+
+// after restore_state_buffers: what the context needs besides to step on its
+// own again, apart from its edge items
+swe_status restore_neighbours(swe_ctx *c)
+{
+    if (c->d_nb) return SWE_OK;
+    HIP_TRY(c, dev_alloc(&c->d_nb, sizeof(int) * 3 * c->stride));
+    HIP_TRY(c, h2d(c, c->d_nb, c->nb_host.data(), sizeof(int) * 3 * c->stride));
     return SWE_OK;
 }
 
@@ -808,6 +821,7 @@ swe_status ensure_step_graph(swe_ctx *c)
     const std::vector<long long> key = step_graph_key(c);
     if (c->step_exec && c->multi_exec && key == c->graph_key) return SWE_OK;
     drop_step_graph(c);
+    if (!c->d_inst) HIP_TRY(c, dev_alloc(&c->d_inst, 2 * sizeof(InstDesc)));
     hipError_t e = build_graph(c, 1, &c->step_graph, &c->step_exec);
     if (e == hipSuccess) e = build_graph(c, GRAPH_STEPS, &c->multi_graph, &c->multi_exec);
     if (e != hipSuccess) {
@@ -1400,26 +1414,26 @@ swe_status group_by_lists(swe_ctx *c)
     return SWE_OK;
 }
 
-// Device bytes of the arrays a context keeps as long as it has a mesh: vertex
-// and neighbour ids, neighbour edges, orders, caller's numbering, vertices,
-// flags, clock, mass reduction scratch.
+// Device bytes of the arrays a context keeps as long as it has a mesh, also
+// while resident in a batch: vertex ids, neighbour edges, orders, caller's
+// numbering, vertices, flags, mass reduction scratch.
 int64_t kept_bytes(int64_t ne, int64_t nv)
 {
     const int64_t S = (ne + BLOCK - 1) / BLOCK * BLOCK;
-    return 2 * 3 * 4 * S + 2 * S + 4 * S + 32 * nv + 12 + 2 * (int64_t)sizeof(InstDesc) + 8 * (S / BLOCK + 2);
+    return 3 * 4 * S + 2 * S + 4 * S + 32 * nv + 12 + 8 * (S / BLOCK + 2);
 }
 
-// Device bytes of a context's state: C0, C1, U0, U1, the right-hand-side
-// scratch, the shared-flux kernel's edge items (at most 3 per element) and the
-// tiles of the one-launch step (at least 128 elements each, 64 on meshes that
-// do not fill the CUs).
+// Device bytes of what it holds besides on its own before it steps: C0, C1, U0,
+// U1, the right-hand-side scratch, neighbour ids and the shared-flux kernel's
+// edge items (at most two per lane of a block, or the mesh has none).  Its first
+// steps may add the tiles of the one-launch step (at least 128 elements each,
+// 64 on meshes that do not fill the CUs) and a graph's clock.
 int64_t state_bytes(int64_t ne, int p, bool fp32)
 {
     const int64_t S = (ne + BLOCK - 1) / BLOCK * BLOCK;
     const int64_t K = K_OF[p], w = fp32 ? 4 : 8;
-    int64_t b = (2 * 3 * K + 2 * 2 * K + 3 * K) * S * w;
-    if (stage_sh_supported(p, fp32))
-        b += 3 * 4 * S + 4 * (S / BLOCK + 1) + (int64_t)TILE_BYTES * (S / (S <= 65536 ? 64 : 128) + 1);
+    int64_t b = (2 * 3 * K + 2 * 2 * K + 3 * K) * S * w + 3 * 4 * S;
+    if (stage_sh_supported(p, fp32)) b += 2 * 4 * S + 4 * (S / BLOCK + 1);
     return b;
 }
 
@@ -1680,7 +1694,6 @@ swe_status swe_set_mesh(swe_ctx *c, int64_t nv, const double *vxy, int64_t ne, c
     }
     HIP_TRY(c, dev_alloc(&c->d_L, w * 3 * K * S));
     HIP_TRY(c, dev_alloc(&c->d_flag, 3 * sizeof(int)));   // failure flag; two words for transfers and set-up
-    HIP_TRY(c, dev_alloc(&c->d_inst, 2 * sizeof(InstDesc)));
     HIP_TRY(c, dzero(c, c->d_flag, sizeof(int)));
     HIP_TRY(c, dev_alloc(&c->d_part, sizeof(double) * (mass_partials((int)ne) + 1)));
     HIP_TRY(c, dev_alloc(&c->d_mass, sizeof(double)));
@@ -2602,7 +2615,7 @@ void swe_batch_destroy(swe_batch *b)
             c->t = b->h_inst[i].t;
             c->batch = nullptr;
             c->slot = -1;
-            (void)build_items(c);
+            if (restore_neighbours(c) == SWE_OK) (void)build_items(c);
         }
     drop_graph(b);
     std::vector<void *> ptrs = {b->d_inst, b->d_flags, b->d_ntiles, b->d_natiles, b->d_vtx};
@@ -2860,7 +2873,8 @@ swe_status swe_batch_retire(swe_batch *b, int32_t slot)
     m = swe_batch::Member();
     c->batch = nullptr;
     c->slot = -1;
-    st = build_items(c);   // the context can step on its own again
+    st = restore_neighbours(c);
+    if (st == SWE_OK) st = build_items(c);   // the context can step on its own again
     if (st) return bfail(b, st, c->err);
     // an order (or the whole batch) without members holds no pool
     bool any = false, any_order = false;

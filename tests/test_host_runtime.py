@@ -106,3 +106,47 @@ def test_tiles_are_built_by_the_call_that_uses_them(lib):
             ctx.step(2, 1.0)
             assert count("tile builds") == 2 and count("one-launch steps") == 10
     """)
+
+
+# swe_footprint_bytes before the one-launch step and the device-side transfers,
+# for ne x p = 0..3 x (FP64, FP32): a request admitted then is admitted now.
+FOOTPRINTS = {
+    288: [89068, 68588, 189784, 115700, 349528, 189784, 562520, 296280],
+    22050: [4396892, 3506012, 8511636, 5555384, 15460500, 8511636, 24725652, 13144212],
+    65536: [12956044, 10334604, 25054528, 16364940, 45501760, 25054528, 72764736, 38686016],
+    260642: [51490588, 41056028, 99688132, 65059592, 181077700, 99688132, 289597124, 153947844],
+}
+
+
+def test_footprints_are_no_larger_than_they_were(lib):
+    host_runtime.run(lib, f"""
+        for ne, old in {FOOTPRINTS!r}.items():
+            new = [swe.swe_footprint_bytes(ne, p, prec) for p in range(4) for prec in (0, 1)]
+            assert all(a <= b for a, b in zip(new, old)), (ne, new, old)
+            assert all(a >= 0.85 * b for a, b in zip(new, old)), (ne, new, old)
+    """)
+
+
+def test_footprints_bound_what_is_held(lib):
+    """Alone after set_mesh and set_state, and resident in an empty batch."""
+    host_runtime.run(lib, """
+        for p in range(4):
+            for prec in (0, 1):
+                prob = I.config_c2(n=21, p=p)
+                bound = swe.swe_footprint_bytes(prob.mesh.ne, p, prec)
+                before = count("bytes")
+                with swe.context_for(prob, precision=prec) as ctx:
+                    ctx.set_state(np.zeros((ctx.ne, 3, ctx.K)))
+                    assert 0 < count("bytes") - before <= bound, (p, prec)
+                    with swe.Batch(precision=prec, budget_bytes=64 << 20, max_instances=2) as b:
+                        empty = count("bytes")
+                        b.admit(ctx, 5, 1.0)
+                        b.tick(5)
+                        assert b.free_bytes() >= (64 << 20) - bound
+                        # the batch's own fixed arrays came before, the context's state buffers went
+                        own = 2 * 1024
+                        assert count("bytes") - before <= bound + own, (p, prec)
+                        b.retire(0)
+                        assert count("bytes") == empty and b.free_bytes() == 64 << 20
+                    ctx.step(4, 1.0)
+    """)
