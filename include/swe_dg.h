@@ -176,6 +176,18 @@ swe_status swe_set_source(swe_ctx *ctx, const double *coef);
  * stream is being captured (that call's steps then take two launches each). */
 swe_status swe_step(swe_ctx *ctx, int64_t nsteps, double dt);
 
+/* The form that a swe_step of several steps takes on the context as it is now
+ * (any output may be NULL): the elements per tile and the groups of edge waves
+ * of the one-launch step (0 without it, and before the first call that can use
+ * it). */
+enum { SWE_FORM_STAGES = 0,      /* launches or a graph per stage */
+       SWE_FORM_STEP = 1,        /* one launch per step */
+       SWE_FORM_STEP_ROLES = 2,  /* the same, waves of a block with roles */
+       SWE_FORM_STAGE_ONE = 3,   /* order-partitioned graph, one launch per stage */
+       SWE_FORM_CHAIN = 4,       /* separated or partitioned graph, one chain */
+       SWE_FORM_BRANCHES = 5 };  /* separated or partitioned graph with branches */
+swe_status swe_step_form(const swe_ctx *ctx, int *form, int *tile, int *flux_groups);
+
 /* Wait for queued work; returns SWE_ESTATE if a stage produced a non-finite
  * value or a non-positive element-mean depth. */
 swe_status swe_sync(swe_ctx *ctx);

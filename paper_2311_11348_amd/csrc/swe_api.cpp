@@ -439,6 +439,14 @@ hipError_t enqueue_stage(swe_ctx *c, int mode, int in, int out, double tstage, d
 
 bool separated(const swe_ctx *c) { return c->cfg.separate && c->cfg.p_base < c->cfg.p_max; }
 
+// Graphs pay off where a step has many dependent kernels (order-separated and
+// order-partitioned steps); a fused step is one or two plain launches; a
+// heterogeneous stage waits for the host in the middle: launches.
+bool steps_by_graph(const swe_ctx *c)
+{
+    return c->ncon <= 4 && !c->cfg.hetero && (c->cfg.step_graph == 2 || (c->cfg.step_graph == 1 && separated(c)));
+}
+
 // Both stages of a step in one launch: the fused scheme on a uniform order
 // with nothing between the stages.  A call's steps run in pairs (state buffer
 // 0 -> 1 -> 0), so the state rests in buffer 0 as ever; the last of an odd
@@ -1883,6 +1891,27 @@ swe_status swe_set_source(swe_ctx *c, const double *coef)
     return SWE_OK;
 }
 
+swe_status swe_step_form(const swe_ctx *c, int *form, int *tile, int *flux_groups)
+{
+    if (!c) return SWE_EINVAL;
+    if (!c->have_mesh) return SWE_EINVAL;
+    int f = SWE_FORM_STAGES, len = 0, groups = 0;
+    if (one_launch_steps(c)) {
+        len = c->tiles.len;
+        groups = step_flux_groups(c->cfg.p_max, c->fp32, (int)((c->ne + len - 1) / len), c->ncu);
+        f = groups ? SWE_FORM_STEP_ROLES : SWE_FORM_STEP;
+    } else if (separated(c) && steps_by_graph(c)) {
+        if (c->cfg.separate == 2 && one_launch_partitioned(c, c->grouped ? c->n_unlisted : c->ne))
+            f = SWE_FORM_STAGE_ONE;
+        else
+            f = one_chain(c) ? SWE_FORM_CHAIN : SWE_FORM_BRANCHES;
+    }
+    if (form) *form = f;
+    if (tile) *tile = len;
+    if (flux_groups) *flux_groups = groups;
+    return SWE_OK;
+}
+
 swe_status swe_step(swe_ctx *c, int64_t nsteps, double dt)
 {
     if (!c) return SWE_EINVAL;
@@ -1897,12 +1926,7 @@ swe_status swe_step(swe_ctx *c, int64_t nsteps, double dt)
     if (c->cfg.hetero && (!c->grouped || c->d_src))
         return fail(c, SWE_EINVAL, "heterogeneous stages need a static order map (swe_set_order) and no extra source");
     if (swe_status st = ready_tiles(c, nsteps)) return st;
-    // graphs pay off where a step has many dependent kernels (order-separated
-    // and order-partitioned steps); a fused step is one or two plain launches;
-    // a heterogeneous stage waits for the host in the middle: launches
-    const bool graph = c->ncon <= 4 && !c->cfg.hetero &&
-                       (c->cfg.step_graph == 2 || (c->cfg.step_graph == 1 && separated(c)));
-    if (graph) {
+    if (steps_by_graph(c)) {
         swe_status st = ensure_step_graph(c);
         if (st != SWE_OK) return st;
         InstDesc d;

@@ -185,6 +185,8 @@ hipError_t launch_stage_sh(int p, bool fp32, int mode, const void *args, const u
 // first stage, xihat2 the open-sea elevation of the second, ncu the device's
 // compute units (a mesh of at most one tile each takes the kernel with roles)
 hipError_t launch_step_sh(int p, bool fp32, const void *args, const TileView &tv, double xihat2, int ncu, Sink &k);
+// groups of edge waves of the kernel that launch_step_sh picks; 0: no roles
+int step_flux_groups(int p, bool fp32, int tiles, int ncu);
 // tile data of the mesh's tiles; over[0]: lanes by which the fullest is beyond
 // a block, over[1]: set if some tile does not fit for another reason
 hipError_t launch_build_tiles(const MeshView &m, int ne, const TileView &tv, int *over, hipStream_t s);

@@ -646,6 +646,16 @@ __global__ void __launch_bounds__(BLOCK) k_build_tiles(MeshView m, int ne, TileV
 
 }  // namespace
 
+// flux groups of the kernel that `tiles` tiles take on ncu compute units; 0: one
+// group of waves for everything
+template <int P, typename Real>
+int step_groups(int tiles, int ncu)
+{
+    if (tiles <= ncu && flux_groups<P, Real>() > 0) return flux_groups<P, Real>();
+    // order 1: two blocks of one flux group each share a CU
+    return P == 1 && tiles <= 2 * ncu ? 1 : 0;
+}
+
 template <int P, typename Real>
 hipError_t step_sh_p(const void *args, const TileView &tv, double xihat2, int ncu, Sink &k)
 {
@@ -654,14 +664,14 @@ hipError_t step_sh_p(const void *args, const TileView &tv, double xihat2, int nc
     void *kargs[] = {&a, &t, &xihat2};
     const dim3 grid((a.m.ne + t.len - 1) / t.len);
     constexpr int ng = flux_groups<P, Real>();
+    const int groups = step_groups<P, Real>((int)grid.x, ncu);
     if constexpr (ng > 0) {
-        if ((int)grid.x <= ncu)
+        if (groups == ng)
             return emit(k, reinterpret_cast<const void *>(&k_step_roles<P, Real, ng>), grid, dim3((1 + ng) * BLOCK),
                         kargs);
     }
-    // order 1: two blocks of one flux group each share a CU
     if constexpr (P == 1) {
-        if ((int)grid.x <= 2 * ncu)
+        if (groups == 1)
             return emit(k, reinterpret_cast<const void *>(&k_step_roles<P, Real, 1>), grid, dim3(2 * BLOCK), kargs);
     }
     return emit(k, reinterpret_cast<const void *>(&k_step_sh<P, Real>), grid, dim3(BLOCK), kargs);
@@ -676,6 +686,16 @@ hipError_t launch_step_sh(int p, bool fp32, const void *args, const TileView &tv
     case 3: return fp32 ? step_sh_p<3, float>(args, tv, xihat2, ncu, k) : step_sh_p<3, double>(args, tv, xihat2, ncu, k);
     }
     return hipErrorInvalidValue;
+}
+
+int step_flux_groups(int p, bool fp32, int tiles, int ncu)
+{
+    switch (p) {
+    case 1: return fp32 ? step_groups<1, float>(tiles, ncu) : step_groups<1, double>(tiles, ncu);
+    case 2: return fp32 ? step_groups<2, float>(tiles, ncu) : step_groups<2, double>(tiles, ncu);
+    case 3: return fp32 ? step_groups<3, float>(tiles, ncu) : step_groups<3, double>(tiles, ncu);
+    }
+    return 0;
 }
 
 hipError_t launch_build_tiles(const MeshView &m, int ne, const TileView &tv, int *over, hipStream_t s)

@@ -17,6 +17,7 @@ LIB_PATH = os.path.join(HERE, "_lib", "libswe_hip.so")
 
 SWE_OK, SWE_EINVAL, SWE_ENOMEM, SWE_EDEVICE, SWE_ESTATE, SWE_EUNSUPPORTED = 0, -1, -2, -3, -4, -5
 SWE_FP64, SWE_FP32_WB = 0, 1
+FORM_STAGES, FORM_STEP, FORM_STEP_ROLES, FORM_STAGE_ONE, FORM_CHAIN, FORM_BRANCHES = range(6)
 SWE_NQP = 36
 K_OF_P = (1, 3, 6, 10)
 _NAMES = {0: "SWE_OK", -1: "SWE_EINVAL", -2: "SWE_ENOMEM", -3: "SWE_EDEVICE", -4: "SWE_ESTATE",
@@ -65,6 +66,7 @@ def lib() -> C.CDLL:
         "swe_set_state_points": (C.c_int, [vp, C.c_double, dp]),
         "swe_set_source": (C.c_int, [vp, dp]),
         "swe_step": (C.c_int, [vp, i64, C.c_double]),
+        "swe_step_form": (C.c_int, [vp, C.POINTER(C.c_int), C.POINTER(C.c_int), C.POINTER(C.c_int)]),
         "swe_sync": (C.c_int, [vp]),
         "swe_get_state": (C.c_int, [vp, dp, dp]),
         "swe_mass": (C.c_int, [vp, dp]),
@@ -236,6 +238,12 @@ class Context:
 
     def sync(self):
         self._check(self.L.swe_sync(self.h))
+
+    def step_form(self):
+        """(form, elements per tile, groups of edge waves) of a several-step call now."""
+        f, tile, groups = C.c_int(), C.c_int(), C.c_int()
+        self._check(self.L.swe_step_form(self.h, C.byref(f), C.byref(tile), C.byref(groups)))
+        return f.value, tile.value, groups.value
 
     def state(self):
         c = np.empty((self.ne, 3, self.K))   # written in full
