@@ -131,6 +131,14 @@ std::shared_mutex graph_calls;
 typedef std::lock_guard<std::shared_mutex> GraphCall;
 typedef std::shared_lock<std::shared_mutex> OtherCall;
 
+// While one is alive, this thread's allocations are no concern of a stream
+// capture that another thread has under way.
+struct OwnCaptureRules {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    OwnCaptureRules() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~OwnCaptureRules() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
 template <typename T>
 hipError_t dev_alloc(T **p, size_t n)
 {
@@ -1037,6 +1045,7 @@ swe_status download(swe_ctx *c, const void *src, int stride, int first, int ncom
         std::unique_lock<std::mutex> u(ring_use, std::try_to_lock);
         if (u.owns_lock()) {
             if (!ring_mem && sizeof(double) * n * (size_t)c->ne >= RING_FROM) {
+                OwnCaptureRules rules;
                 void *q = nullptr;
                 if (pinned_alloc(&q, RING_SLOTS * RING_SLOT, hipHostMallocPortable | hipHostMallocCoherent) == hipSuccess)
                     ring_mem = static_cast<char *>(q);
@@ -1191,14 +1200,6 @@ swe_status build_tiles(swe_ctx *c)
     }
     return SWE_OK;
 }
-
-// While one is alive, this thread's allocations are no concern of a stream
-// capture that another thread has under way.
-struct OwnCaptureRules {
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    OwnCaptureRules() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
-    ~OwnCaptureRules() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
-};
 
 // Tiles for a call of nsteps steps: built by the first call that can use them,
 // so that a context which only goes through a batch has none.  Building waits

@@ -32,6 +32,7 @@ std::map<std::string, long> counts;
 std::map<void *, size_t> sizes;
 std::atomic<int> in_graph_call{0};
 thread_local bool refuse = false;
+thread_local hipStreamCaptureMode mode = hipStreamCaptureModeGlobal;
 
 // held while the maps above are used, whose own allocations are not refused
 struct Model {
@@ -87,7 +88,7 @@ hipError_t alloc(void **p, size_t n)
     Model l;
     sizes[*p] = n;
     counts["bytes"] += (long)n;
-    counts["allocations"] += 1;
+    if (mode != hipStreamCaptureModeRelaxed) counts["allocations a capture elsewhere forbids"] += 1;
     return hipSuccess;
 }
 
@@ -138,6 +139,7 @@ hipError_t hipHostMalloc(void **p, size_t n, unsigned flags)
     OtherCall call;
     Model l;
     counts["pinned allocations"] += 1;
+    if (mode != hipStreamCaptureModeRelaxed) counts["allocations a capture elsewhere forbids"] += 1;
     if (!(flags & hipHostMallocCoherent)) counts["pinned allocations not coherent"] += 1;
     *p = calloc(1, n);
     return hipSuccess;
@@ -185,7 +187,11 @@ hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *st)
     *st = hipStreamCaptureStatusNone;
     return hipSuccess;
 }
-hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode *) { return hipSuccess; }
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode *m)
+{
+    std::swap(mode, *m);
+    return hipSuccess;
+}
 hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned)
 {
     Model l;

@@ -82,3 +82,41 @@ def test_static_form_and_launches_agree(n, separate, lo, precision, form):
     assert ta == tb
     assert np.linalg.norm(b) > 0
     assert np.linalg.norm(a - b) <= (1e-12 if precision == F64 else 1e-5) * np.linalg.norm(b)
+
+
+def test_steps_under_capture():
+    """The first several-step call on a stream that is being captured (it has
+    no tiles yet, and must not make them there), then with tiles; replayed with
+    eager work and synchronisations between, each replay against plain calls."""
+    import torch
+    prob = I.config_c3(n=20)
+    prob.adapt, prob.p_base, prob.p_max = 0, 2, 2
+    prob.p[:] = 2
+    c0 = I.random_state(prob.mesh, prob.p, 2, 3, prob.hb_vertex, 0.2, 0.5, 0.1)
+    dt = prob.dt()
+    want = []
+    with swe.context_for(prob) as ctx:
+        ctx.set_state(c0)
+        for _ in range(7):
+            ctx.step(2, dt)
+            want.append(ctx.state()[0])
+    s = torch.cuda.Stream()
+    with swe.context_for(prob, stream_base=s.cuda_stream) as ctx:
+        ctx.set_state(c0)
+        done = 0
+        for tiles in (False, True):
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(g, stream=s):
+                ctx.step(2, dt)
+            assert (ctx.step_form()[1] > 0) == tiles
+            for _ in range(3):
+                with torch.cuda.stream(s):
+                    g.replay()
+                ctx.sync()
+                torch.zeros(1000, device="cuda").sum().item()
+                assert np.array_equal(ctx.state()[0], want[done])
+                done += 1
+            if not tiles:
+                ctx.step(2, dt)
+                assert np.array_equal(ctx.state()[0], want[done])
+                done += 1

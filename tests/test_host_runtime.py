@@ -150,3 +150,18 @@ def test_footprints_bound_what_is_held(lib):
                         assert count("bytes") == empty and b.free_bytes() == 64 << 20
                     ctx.step(4, 1.0)
     """)
+
+
+def test_reading_and_stepping_leave_captures_elsewhere_alone(lib):
+    """A read-back and a step made no allocation when both were host loops and
+    stage launches; those they make now must not break a stream capture that
+    another thread (or this one, on another stream) has under way."""
+    host_runtime.run(lib, """
+        with swe.context_for(I.config_c2(n=160, p=2)) as ctx:
+            ctx.set_state(np.zeros((ctx.ne, 3, ctx.K)))
+            before = count("allocations a capture elsewhere forbids")
+            ctx.step(4, 1.0)
+            ctx.state()
+            assert count("tile builds") == 1 and count("pinned allocations") == 1
+            assert count("allocations a capture elsewhere forbids") == before
+    """)
