@@ -95,11 +95,11 @@ def kernel_bytes_per_element(p: int, word: int, nv: int, ne: int) -> float:
     return state + geo
 
 
-def step_bytes_per_element(p: int, word: int, nv: int, ne: int) -> float:
+def step_bytes_per_element(p: int, word: int, nv: int, ne: int, tile: int) -> float:
     """A whole step in one launch: read c and u (5K), write c and u (5K), and
-    the tile's data (4,864 B of edge items, neighbours and vertex ids per 192
-    elements) and the vertex records."""
-    return 10 * K_OF_P[p] * word + 4864 / 192 + 32.0 * nv / ne
+    the tile's data (4,864 B of edge items, neighbours and vertex ids per
+    `tile` elements) and the vertex records."""
+    return 10 * K_OF_P[p] * word + 4864 / tile + 32.0 * nv / ne
 
 
 # Vector peaks of the MI355X (256 CUs at 2.4 GHz): FP32 157.3 TFLOP/s with
@@ -323,6 +323,7 @@ def run_uniform(prob, precision, steps, warmup):
     ctx.sync()
     torch.cuda.synchronize()
     ms = timed_steps(ctx, stream, steps, dt)
+    form, tile, _ = ctx.step_form()
     ctx.close()
     p = int(prob.p_max)
     ne, nv = prob.mesh.ne, prob.mesh.nv
@@ -331,17 +332,18 @@ def run_uniform(prob, precision, steps, warmup):
     # every launch of the timed region is this kernel (back to back on the
     # library stream; an odd number of steps ends with two stage launches), so
     # the event-timed region / launches is its average launch duration, launch
-    # gaps included.  One launch is a whole step (both stages) at orders 1 to 3,
-    # except FP64 p = 3, where the mesh decides: priced per stage
-    whole = 1 <= p <= (2 if word == 8 else 3)
+    # gaps included.  One launch is a whole step (both stages) where the mesh
+    # takes that form
+    whole = form in (swe.FORM_STEP, swe.FORM_STEP_ROLES)
+    step_kernel = "k_step_roles" if form == swe.FORM_STEP_ROLES else "k_step_sh"
     stages = 2 if whole else 1
     stage_s = ms * 1e-3 / (2 * steps)
     launch_s = stage_s * stages
     bpe = stage_bytes_per_element(p, word)
-    kbpe = step_bytes_per_element(p, word, nv, ne) if whole else kernel_bytes_per_element(p, word, nv, ne)
+    kbpe = step_bytes_per_element(p, word, nv, ne, tile) if whole else kernel_bytes_per_element(p, word, nv, ne)
     achieved = bpe * ne / stage_s / 1e9
     real = "double" if word == 8 else "float"
-    traffic = measured_traffic([f"k_step_sh<{p}, {real}>"]) if p == 2 and ne == 524288 else None
+    traffic = measured_traffic([f"{step_kernel}<{p}, {real}>"]) if whole and p == 2 and ne == 524288 else None
     compute = compute_roofline(p, word == 4, ne, stage_s)
     compute["flop_per_launch"] *= stages
     return {"value": dof / stage_s, "ms_per_step": ms / steps,
@@ -349,7 +351,7 @@ def run_uniform(prob, precision, steps, warmup):
                          "frac": achieved / HBM_PEAK_GBS,
                          "traffic": traffic / 1e9 / launch_s if traffic is not None else None,
                          "traffic_bytes_per_launch": traffic,
-                         "kernel": f"k_step_sh<{p},{real}> (both stages of a step, edge fluxes shared within a tile)"
+                         "kernel": f"{step_kernel}<{p},{real}> (both stages of a step, edge fluxes shared within a tile)"
                                    if whole else
                                    f"k_stage_sh<{p},{real}> (fused stage, edge fluxes shared within a block)"
                                    if p >= 1 else f"k_stage<{p},{real}> (fused stage, element gather)",
@@ -370,7 +372,7 @@ def run_separated(prob, precision, steps, warmup, separate=1, chunk=50, hetero=0
     epilogue; hetero=1: the corrections on the host's cores) or
     order-partitioned scheme (separate=2: base elements and each order's
     listed elements), optionally adaptive.  A static order map runs the
-    base and list work on two graph branches, an adaptive one as one chain
+    base and list work on graph branches, an adaptive one as one chain
     per step.  DOF counts follow the order map, read between timed chunks."""
     import numpy as np
     import torch

@@ -78,12 +78,12 @@ struct StageArgs {
     int *listw;          // [4][lcap] lists being rebuilt by the order update
     int *cntw;           // [4] their lengths
     Real *Calt, *Ualt;   // the other state/velocity buffer (order update clears dropped modes)
-    // batched instance launched on its own: element indices start at e_off in
-    // the pooled arrays; step, open-sea elevation and run flag come from inst
+    // step graphs: the step's clock (step size, open-sea elevation, run flag), or null
     const struct InstDesc *inst;
-    struct InstDesc *next;         // list kernels up to order 2, last stage of a step: where the next step's clock goes, or null
-                                   // (flag is then its `late`)
-    int e_off;
+    // list kernels up to order 2, last stage of a step: where the next step's
+    // clock goes (flag is then its `late`), or null
+    struct InstDesc *next;
+    int e_off;           // first element of a launch over a part of the elements (m.ne: how many)
     int stage;           // with inst: which stage time of the step (0 or 1) a kernel without MODE uses;
                          // one-launch step: 1 for the second of a pair, whose result goes to state buffer 0
     int skip_listed;     // base kernel of the order-partitioned scheme: listed elements are not its work
@@ -244,16 +244,16 @@ int mass_partials(int ne);
 hipError_t launch_batch_stage(int p, bool fp32, int mode, int tile, const BatchArgs &b, int grid, Sink &k);
 // *to = *from advanced by a step (from may equal to), both with `late` clear
 hipError_t launch_next_clock(InstDesc *from, InstDesc *to, const int *flag, Sink &k);
-// clocks of the instances of one order (order < 0: of every instance)
+// clocks of the instances of one order
 hipError_t launch_batch_clock(InstDesc *inst, const int *flags, int n, int order, Sink &k);
 // write one instance descriptor in stream order (no host buffer outlives the call)
 hipError_t launch_inst_set(InstDesc *inst, const InstDesc &v, hipStream_t s);
-// copy an instance's mesh arrays into a pool, offsetting vertex and element ids
 // batched shared-flux stage (one 256-element tile per block; orders with
 // stage_sh_supported); items placed in the pool by launch_place_items
 hipError_t launch_batch_stage_sh(int p, bool fp32, int mode, const BatchArgs &b, int grid, Sink &k);
 hipError_t launch_place_items(const unsigned *items, const int *item_off, int nblk, const PoolView &pool, int first,
                               hipStream_t s);
+// copy an instance's mesh arrays into a pool, offsetting vertex and element ids
 hipError_t launch_relocate(const int *ev, const int *nb, const unsigned char *nbk, const signed char *ep, int ne,
                            int stride, const PoolView &pool, int first, int vbase, hipStream_t s);
 // order update of a batch's indicator-driven members of one order class:

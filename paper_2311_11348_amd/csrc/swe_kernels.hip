@@ -135,7 +135,7 @@ k_stage(StageArgs<Real> a)
     if (le >= (unsigned)a.m.ne) return;
     double xihat = a.xihat, dt = a.dt;
     if (a.inst) {
-        // one instance of a batch: its clock lives on the device
+        // the clock of a replayed step lives on the device
         if (step_stopped(a)) return;
         xihat = MODE == MODE_STAGE2 ? a.inst->xh[1] : a.inst->xh[0];
         dt = a.inst->dt;
@@ -338,7 +338,7 @@ __global__ void k_next_clock(InstDesc *from, InstDesc *to, const int *flag)
 __global__ void __launch_bounds__(BLOCK) k_batch_clock(InstDesc *inst, const int *flags, int n, int order)
 {
     const int i = blockIdx.x * BLOCK + threadIdx.x;
-    if (i >= n || (order >= 0 && inst[i].order != order)) return;
+    if (i >= n || inst[i].order != order) return;
     clock_advance(inst[i], flags[i]);
 }
 

@@ -17,21 +17,22 @@ namespace {
 // launches bit for bit.
 //
 // A tile is one block of 256 lanes, one local element each: the owned ones,
-// then the ring.  With 192 owned elements (three waves) the ring of a
-// Morton-ordered triangulation is 35-50 elements and fits the fourth wave,
-// which sits out the second stage's element work: 1.17 times the element
-// work of two separate stages for about half their memory traffic.
+// then the ring.  Of a Morton-ordered structured triangulation a tile of 176 to
+// 192 elements has a ring of 52 to 55 on average and of 64 to 74 at most (sides
+// 160 to 512), so the mesh's longest ring sets its tiles' length: 192 at side
+// 512, 184 or 176 at most others.  The ring fits the fourth wave but for a few
+// lanes, and that wave sits out the second stage's element work: 1.14 to 1.15
+// times the element work of two separate stages for about half their traffic.
 // Bound by VALU issue at FP32 p = 2 (74 % of the SIMDs' cycles), by latency at
 // two blocks and one per CU in FP64 p = 2 and 3.  Two launches / one, us a
 // step: FP32 p = 1 50.3 / 39.8 and p = 2 84.3 / 73.5 (524,288 elements), FP64
 // p = 1 86 / 64 and p = 2 158 / 142 (524,288), 84 / 81 (260,642), p = 3 FP32
 // 33.1 / 26.0 and FP64 49.7 / 38.5 (39,200).  The two stages are unrolled: as
 // a loop the invariants of both live across it (FP64 p = 2 spilled, 110 us
-// at 260,642 elements).  Tile
-// data is built on the device (k_build_tiles) when the mesh is set: edge
-// items, ring and outside neighbours, and the tile's vertices, which are
-// staged in LDS so that neither the edge pass nor the element pass reads
-// vertex ids or vertices from memory.
+// at 260,642 elements).  Tile data is built on the device (k_build_tiles) by the
+// first call that steps this way: edge items, ring and outside neighbours, and
+// the tile's vertices, which are staged in LDS so that neither the edge pass nor
+// the element pass reads vertex ids or vertices from memory.
 template <int P, typename Real, bool BOTH>
 struct StepLds {
     ShLds<P, Real, BOTH> S;
