@@ -189,7 +189,9 @@ enum { SWE_FORM_STAGES = 0,      /* launches or a graph per stage */
 swe_status swe_step_form(const swe_ctx *ctx, int *form, int *tile, int *flux_groups);
 
 /* Wait for queued work; returns SWE_ESTATE if a stage produced a non-finite
- * value or a non-positive element-mean depth. */
+ * value or a non-positive element-mean depth.  Where steps are replayed graphs,
+ * the state is then that of the step in which this first happened (the steps
+ * after it do not run); plain launches run to the end of their swe_step. */
 swe_status swe_sync(swe_ctx *ctx);
 
 /* Current state coef_out[ne][3][K(p_max)] and time (synchronises). */

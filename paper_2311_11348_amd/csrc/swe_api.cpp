@@ -965,9 +965,10 @@ hipError_t ring_download(swe_ctx *c, const void *src, int stride, int first, int
     const size_t row = sizeof(double) * (size_t)n;
     hipEvent_t ev[RING_SLOTS] = {};
     hipError_t e = hipSuccess;
-    // (the host reads the slot after the event: a release to the system)
+    // (coherent memory needs no release of its own before the host reads it: events
+    // with one took 5 us a part more)
     for (auto &x : ev)
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&x, hipEventDisableTiming | hipEventReleaseToSystem);
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&x, hipEventDisableTiming);
     std::atomic<int64_t> packed{0};             // parts in their slots
     std::atomic<bool> stop{false};
     std::atomic<int64_t> copied[RING_SLOTS];    // of each slot: copies made by any thread, nth per part

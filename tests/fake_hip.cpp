@@ -27,7 +27,6 @@ std::mutex mx;
 std::map<void *, Stream> streams;
 std::map<void *, Waits> events;                    // what an event was recorded after
 std::map<void *, Waits> execs;                     // launches of a graph
-std::map<void *, unsigned> event_flags;
 std::map<std::string, long> counts;
 std::map<void *, size_t> sizes;
 std::atomic<int> in_graph_call{0};
@@ -198,13 +197,7 @@ hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned)
     for (const auto &w : events[e]) streams[s].waits.insert(w);
     return hipSuccess;
 }
-hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned flags)
-{
-    handle(e);
-    Model l;
-    event_flags[*e] = flags;
-    return hipSuccess;
-}
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return handle(e); }
 hipError_t hipEventCreate(hipEvent_t *e) { return hipEventCreateWithFlags(e, 0); }
 hipError_t hipEventDestroy(hipEvent_t e)
 {
@@ -221,7 +214,6 @@ hipError_t hipEventRecord(hipEvent_t e, hipStream_t s)
 hipError_t hipEventSynchronize(hipEvent_t e)
 {
     Model l;
-    if (!(event_flags[e] & hipEventReleaseToSystem)) counts["host waits on events without a system release"] += 1;
     for (const auto &w : Waits(events[e])) done(w.first, w.second);
     return hipSuccess;
 }
