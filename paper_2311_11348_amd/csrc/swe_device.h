@@ -809,12 +809,14 @@ __device__ __forceinline__ Real store_state(const StageArgs<Real> &a, unsigned o
 // sets it runs beside kernels which may still find a failure; they write it to
 // the next clock's `late`, which is final when the next step starts).  A step
 // that does not run for the latter reason reports a failure itself, so that the
-// one after it does not run either.  Uniform over the grid.
-template <typename Real>
+// one after it does not run either.  Uniform over the grid.  LATE: the kernel
+// has a place in such graphs (base orders 0 and 1, lists up to order 2); in the
+// others the test would only move their code about.
+template <bool LATE, typename Real>
 __device__ __forceinline__ bool step_stopped(const StageArgs<Real> &a)
 {
-    if (a.inst->run && !a.inst->late) return false;
-    if (a.inst->late) a.flag[0] = 1;
+    if (a.inst->run && !(LATE && a.inst->late)) return false;
+    if (LATE && a.inst->late) a.flag[0] = 1;
     return true;
 }
 

@@ -55,7 +55,7 @@ k_stage_sh(StageArgs<Real> a, const unsigned *items, const int *item_off)
     double xihat = a.xihat, dt = a.dt;
     if (a.inst) {
         // the step's clock stopped (failure): the whole block leaves before its first barrier
-        if (step_stopped(a)) return;
+        if (step_stopped<P <= 1>(a)) return;
         xihat = MODE == MODE_STAGE2 ? a.inst->xh[1] : a.inst->xh[0];
         dt = a.inst->dt;
     }
@@ -136,7 +136,7 @@ k_stage(StageArgs<Real> a)
     double xihat = a.xihat, dt = a.dt;
     if (a.inst) {
         // the clock of a replayed step lives on the device
-        if (step_stopped(a)) return;
+        if (step_stopped<SEP && P <= 1>(a)) return;
         xihat = MODE == MODE_STAGE2 ? a.inst->xh[1] : a.inst->xh[0];
         dt = a.inst->dt;
     }
@@ -287,17 +287,19 @@ __device__ __forceinline__ double clock_xihat(const InstDesc &I, double t)
 // instance (non-positive depth or a non-finite value) or one whose step
 // budget is spent stops; otherwise the open-sea elevation at the step's two
 // stage times is set and the time advanced.
-__device__ __forceinline__ void clock_advance(InstDesc &I, int flag)
+__device__ __forceinline__ void clock_advance(const InstDesc &I, int flag, InstDesc &to)
 {
     const int run = I.active && I.steps_left > 0 && flag == 0;
-    I.ran = I.run;
-    I.run = run;
+    to.ran = I.run;
+    to.run = run;
     if (!run) return;
-    I.xh[0] = clock_xihat(I, I.t);
-    I.xh[1] = clock_xihat(I, I.t + I.dt);
-    I.t = I.t0 + (double)(I.steps_done + 1) * I.dt;
-    I.steps_done += 1;
-    I.steps_left -= 1;
+    const int done = I.steps_done + 1, left = I.steps_left - 1;
+    const double x0 = clock_xihat(I, I.t), x1 = clock_xihat(I, I.t + I.dt);
+    to.xh[0] = x0;
+    to.xh[1] = x1;
+    to.t = I.t0 + (double)done * I.dt;
+    to.steps_done = done;
+    to.steps_left = left;
 }
 
 // The clock of a step graph's next step, from the current step's: another
@@ -306,15 +308,7 @@ __device__ __forceinline__ void clock_advance(InstDesc &I, int flag)
 // still being found, so the flag is not looked at (see step_stopped).
 __device__ __forceinline__ void next_clock(const InstDesc *from, InstDesc *to)
 {
-    if (threadIdx.x != 0) return;
-    InstDesc v = *from;
-    clock_advance(v, !v.run);
-    to->run = v.run;
-    to->steps_done = v.steps_done;
-    to->steps_left = v.steps_left;
-    to->t = v.t;
-    to->xh[0] = v.xh[0];
-    to->xh[1] = v.xh[1];
+    if (threadIdx.x == 0) clock_advance(*from, !from->run, *to);
 }
 
 // Whether the list kernels of orders up to PN hold that code, for one block
@@ -331,7 +325,7 @@ __global__ void k_next_clock(InstDesc *from, InstDesc *to, const int *flag)
 {
     if (threadIdx.x != 0) return;
     if (to != from) *to = *from;
-    clock_advance(*to, flag[0]);
+    clock_advance(*to, flag[0], *to);
     from->late = to->late = 0;
 }
 
@@ -339,7 +333,7 @@ __global__ void __launch_bounds__(BLOCK) k_batch_clock(InstDesc *inst, const int
 {
     const int i = blockIdx.x * BLOCK + threadIdx.x;
     if (i >= n || inst[i].order != order) return;
-    clock_advance(inst[i], flags[i]);
+    clock_advance(inst[i], flags[i], inst[i]);
 }
 
 // ------------------------------------------------------------ listed elements, every order in one launch
@@ -547,7 +541,7 @@ __device__ __forceinline__ void full_block(const StageArgs<Real> &a, int lo, int
     if (c * (team ? TEAM : BLOCK) >= len) return;
     double xihat = a.xihat, dt = a.dt;
     if (a.inst) {
-        if (step_stopped(a)) return;   // the step's clock stopped (failure); uniform over the block
+        if (step_stopped<clock_in_lists<PN>()>(a)) return;   // the step's clock stopped (failure); uniform over the block
         xihat = MODE == MODE_STAGE2 ? a.inst->xh[1] : a.inst->xh[0];
         dt = a.inst->dt;
     }
@@ -626,7 +620,7 @@ k_part_all(StageArgs<Real> a, int lcap, int nlist, int nsh, int e_end, const uns
     const int blk = xcd_block((int)blockIdx.x - nlist, (int)gridDim.x - nlist);
     double xihat = a.xihat, dt = a.dt;
     if (a.inst) {
-        if (step_stopped(a)) return;   // the step's clock stopped (failure); uniform over the block
+        if (step_stopped<clock_in_lists<PN>()>(a)) return;   // the step's clock stopped (failure); uniform over the block
         xihat = MODE == MODE_STAGE2 ? a.inst->xh[1] : a.inst->xh[0];
         dt = a.inst->dt;
     }
@@ -1101,7 +1095,7 @@ __global__ void __launch_bounds__(BLOCK) k_apply_order(StageArgs<Real> a, const 
     __shared__ int cnt[4][BLOCK / 64];   // listed elements of an order in each wave, then where they go
     const unsigned e = blockIdx.x * BLOCK + threadIdx.x;
     // a step graph's clock (no other thread of this kernel reads the instance)
-    if (clock && e == 0) clock_advance(*clock, flag[0]);
+    if (clock && e == 0) clock_advance(*clock, flag[0], *clock);
     const bool live = e < (unsigned)a.m.ne;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int pn = 0;
@@ -1211,7 +1205,7 @@ __global__ void __launch_bounds__(BLOCK) k_depth_limit(StageArgs<Real> a, double
     const MeshView &m = a.m;
     const unsigned e = blockIdx.x * BLOCK + threadIdx.x;
     if (e >= (unsigned)m.ne) return;
-    if (a.inst && step_stopped(a)) return;   // the step's clock stopped (failure)
+    if (a.inst && step_stopped<true>(a)) return;   // the step's clock stopped (failure)
     const int p = m.ep ? (int)m.ep[e] : PM;
     if (p < 1) return;
     const int Ke = KOFP[p];
