@@ -368,6 +368,7 @@ struct Lanes {
     const InstDesc *inst = nullptr;   // graph: the current step's clock
     InstDesc *next = nullptr;         // and where the step's last list kernel puts the next one's, or null
     int *flag = nullptr;              // and where its failures go
+    int tick = 0;                     // the list kernels see to the clock
     explicit Lanes(swe_ctx *cc) : c(cc)
     {
         a.s = c->s_base;
@@ -401,6 +402,14 @@ struct Lanes {
         if (graph) return a.join(b) && (!rest || a.join(r)) ? hipSuccess : hipErrorInvalidValue;
         const hipError_t e = hipEventRecord(c->ev_corr, c->s_corr);
         return e == hipSuccess ? hipStreamWaitEvent(c->s_base, c->ev_corr, 0) : e;
+    }
+
+    // the last stage's list kernel sees to the clock
+    template <typename Real>
+    void clock(StageArgs<Real> &args) const
+    {
+        args.tick = tick;
+        args.next = next;
     }
 
     // stage time: from the host, or (graph) from the device clock of the step
@@ -712,7 +721,7 @@ hipError_t enqueue_partitioned(Lanes &L, int mode, int in, int out, double tstag
     a.skip_listed = 1;
     const int64_t end = c->grouped ? c->n_unlisted : c->ne;
     if (L.graph && one_launch_partitioned(c, end)) {
-        if (mode == MODE_STAGE2) a.next = L.next;
+        if (mode == MODE_STAGE2) L.clock(a);
         a.list = c->d_list;
         a.count = c->d_cnt;
         const int64_t nsh = c->d_items ? std::min(c->item_blocks, (end + BLOCK - 1) / BLOCK) : 0;
@@ -727,7 +736,7 @@ hipError_t enqueue_partitioned(Lanes &L, int mode, int in, int out, double tstag
     if (e != hipSuccess) return e;
     // the listed elements of every order in one launch on branch B
     a.skip_listed = 0;
-    if (mode == MODE_STAGE2) a.next = L.next;
+    if (mode == MODE_STAGE2) L.clock(a);
     a.list = c->d_list;
     a.count = c->d_cnt;
     e = launch_full_all(b, pm, c->fp32, mode, &a, list_blocks(c), (int)c->ne, L.side());
@@ -816,6 +825,7 @@ hipError_t build_graph(swe_ctx *c, int nsteps, hipGraph_t *g_out, hipGraphExec_t
             InstDesc *now = c->d_inst + (listed ? (nsteps - 1 - s) & 1 : 0);
             if (s == 0 || !listed) e = launch_next_clock(c->d_inst, now, c->d_flag, L.a);
             L.inst = now;
+            L.tick = listed && nsteps > 1;
             L.next = listed && s + 1 < nsteps ? c->d_inst + ((nsteps - 2 - s) & 1) : nullptr;
             L.flag = L.next ? &L.next->late : c->d_flag;
         }

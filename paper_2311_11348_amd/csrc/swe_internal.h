@@ -80,8 +80,10 @@ struct StageArgs {
     Real *Calt, *Ualt;   // the other state/velocity buffer (order update clears dropped modes)
     // step graphs: the step's clock (step size, open-sea elevation, run flag), or null
     const struct InstDesc *inst;
-    // list kernels up to order 2, last stage of a step: where the next step's
-    // clock goes (flag is then its `late`), or null
+    // list kernels up to order 2, last stage of a step: whether one block more
+    // sees to the clock, and where the next step's goes (flag is then its `late`;
+    // null after a graph's last step)
+    int tick;
     struct InstDesc *next;
     int e_off;           // first element of a launch over a part of the elements (m.ne: how many)
     int stage;           // with inst: which stage time of the step (0 or 1) a kernel without MODE uses;

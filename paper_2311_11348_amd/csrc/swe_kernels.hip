@@ -304,11 +304,15 @@ __device__ __forceinline__ void clock_advance(const InstDesc &I, int flag, InstD
 
 // The clock of a step graph's next step, from the current step's: another
 // descriptor, so that a kernel which reads the current one may run meanwhile.
-// It holds the run's constants already.  Failures of the current step are
-// still being found, so the flag is not looked at (see step_stopped).
-__device__ __forceinline__ void next_clock(const InstDesc *from, InstDesc *to)
+// It holds the run's constants already.  Failures of the current step are still
+// being found, so those are not looked at (see step_stopped); one that kept the
+// current step from running is handed on, after a graph's last step (to null)
+// to the run's flag.
+__device__ __forceinline__ void next_clock(const InstDesc *from, InstDesc *to, int *flag)
 {
-    if (threadIdx.x == 0) clock_advance(*from, !from->run, *to);
+    if (threadIdx.x != 0) return;
+    if (to) clock_advance(*from, !from->run || from->late, *to);
+    if (from->late) *(to ? &to->late : flag) = 1;
 }
 
 // Whether the list kernels of orders up to PN hold that code, for one block
@@ -582,7 +586,7 @@ k_full_all(StageArgs<Real> a, int lo, int lcap)
     __shared__ Real sR[3][Ord<PN>::K][PN + 1];
     __shared__ TeamLds<PN, Real> X;
     if constexpr (clock_in_lists<PN>() && MODE == MODE_STAGE2) {
-        if (a.next && blockIdx.x == gridDim.x - 1) return next_clock(a.inst, a.next);
+        if (a.tick && blockIdx.x == gridDim.x - 1) return next_clock(a.inst, a.next, a.flag);
     }
     full_block<PN, Real, MODE>(a, lo, lcap, (int)blockIdx.x, sR, X);
 }
@@ -611,7 +615,7 @@ k_part_all(StageArgs<Real> a, int lcap, int nlist, int nsh, int e_end, const uns
     if ((int)blockIdx.x < nlist) {
         __builtin_amdgcn_s_setprio(2);
         if constexpr (clock_in_lists<PN>() && MODE == MODE_STAGE2) {
-            if (a.next && (int)blockIdx.x == nlist - 1) return next_clock(a.inst, a.next);
+            if (a.tick && (int)blockIdx.x == nlist - 1) return next_clock(a.inst, a.next, a.flag);
         }
         full_block<PN, Real, MODE>(a, B, lcap, (int)blockIdx.x, T.L.sR, T.L.X);
         return;
@@ -1550,8 +1554,8 @@ hipError_t full_all_r(int mode, const void *args, int lo, int nblk, int lcap, Si
 {
     StageArgs<Real> a = *static_cast<const StageArgs<Real> *>(args);
     void *kargs[] = {&a, &lo, &lcap};
-    // (with a clock to advance, one block more for it)
-    const dim3 g((PN - lo + 1) * list_grid(nblk, PN) + (a.next ? 1 : 0)), b(TEAM * TEAM_ROLES);
+    // (one block more for the clock)
+    const dim3 g((PN - lo + 1) * list_grid(nblk, PN) + (a.tick ? 1 : 0)), b(TEAM * TEAM_ROLES);
     return emit(s,
                 mode == MODE_STAGE1 ? reinterpret_cast<const void *>(&k_full_all<PN, Real, MODE_STAGE1>)
                                     : reinterpret_cast<const void *>(&k_full_all<PN, Real, MODE_STAGE2>),
@@ -1565,7 +1569,7 @@ hipError_t part_all_r(int mode, const void *args, int nblk, int lcap, int nsh, i
     StageArgs<Real> a = *static_cast<const StageArgs<Real> *>(args);
     // (a multiple of 8, so that the base blocks keep their XCDs; the last is past
     // every list's end where there is a clock to advance)
-    int nlist = ((PN - B + 1) * list_grid(nblk, PN) + (a.next ? 8 : 7)) / 8 * 8;
+    int nlist = ((PN - B + 1) * list_grid(nblk, PN) + (a.tick ? 8 : 7)) / 8 * 8;
     void *kargs[] = {&a, &lcap, &nlist, &nsh, &e_end, &items, &item_off};
     return emit(s,
                 mode == MODE_STAGE1 ? reinterpret_cast<const void *>(&k_part_all<B, PN, Real, MODE_STAGE1>)
