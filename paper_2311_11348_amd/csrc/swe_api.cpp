@@ -1170,16 +1170,16 @@ bool one_launch_pays(const swe_ctx *c, int len)
     return per_cu == 1 ? 5 * rt < 7 * rb : 2 * rt <= 3 * rb;
 }
 
-// Tiles of the one-launch step for the current numbering, by a device kernel: 192 owned elements each (three waves, the ring
-// in the fourth), or fewer, by eights, where some tile of the mesh is beyond a
-// block (a ring above 64 elements, many boundary edges); below 128 owned
-// elements the ring costs as much as they do, and the mesh keeps two launches
-// per step.  A mesh that leaves CUs without a tile is cut finer, down to 96
-// elements: the tiles' edge items then take one round of the edge waves
-// instead of two, and fewer waves share a SIMD (us a step with 192 / 96
-// elements, 22,050 elements: FP64 p = 1 9.2 / 8.4, p = 2 17.1 / 14.8, p = 3 36.3
-// / 31.3, FP32 p = 2 11.3 / 10.2, p = 3 19.7 / 18.1; 64 elements gain nothing
-// more, and their outside neighbours outnumber them).
+// Tiles of the one-launch step for the current numbering, by a device kernel: 192
+// owned elements each (three waves, the ring in the fourth), or fewer, by eights,
+// where some tile of the mesh is beyond a block (a ring above 64 elements, many
+// boundary edges); below 128 owned elements the ring costs as much as they do,
+// and the mesh keeps two launches per step.  A mesh that leaves CUs without a
+// tile is cut finer, down to 96 elements: the tiles' edge items then take one
+// round of the edge waves instead of two, and fewer waves share a SIMD (us a step
+// with 192 / 96 elements, 22,050 elements: FP64 p = 1 9.2 / 8.4, p = 2 17.1 / 14.8,
+// p = 3 36.3 / 31.3, FP32 p = 2 11.3 / 10.2, p = 3 19.7 / 18.1; 64 elements gain
+// nothing more, and their outside neighbours outnumber them).
 swe_status build_tiles(swe_ctx *c)
 {
     const int64_t fill = (c->ne + c->ncu - 1) / c->ncu;   // elements per CU

@@ -22,7 +22,8 @@ namespace {
 // 160 to 512), so the mesh's longest ring sets its tiles' length: 192 at side
 // 512, 184 or 176 at most others.  The ring fits the fourth wave but for a few
 // lanes, and that wave sits out the second stage's element work: 1.14 to 1.15
-// times the element work of two separate stages for about half their traffic.
+// times the element work of two separate stages (1.17 to 1.2 with the lanes
+// past the ring) for about half their traffic.
 // Bound by VALU issue at FP32 p = 2 (74 % of the SIMDs' cycles), by latency at
 // two blocks and one per CU in FP64 p = 2 and 3.  Two launches / one, us a
 // step: FP32 p = 1 50.3 / 39.8 and p = 2 84.3 / 73.5 (524,288 elements), FP64
