@@ -1184,13 +1184,21 @@ swe_status build_tiles(swe_ctx *c)
 {
     const int64_t fill = (c->ne + c->ncu - 1) / c->ncu;   // elements per CU
     const int start = fill >= 192 ? 192 : std::max(96, (int)(fill + 7) / 8 * 8), least = fill > 192 ? 128 : 64;
+    size_t held = 0;   // tiles there is room for
     for (int len = start; len >= least && one_launch_pays(c, len);) {
         const size_t nt = (size_t)((c->ne + len - 1) / len);
-        if (dev_alloc(&c->d_tiles, nt * TILE_BYTES) != hipSuccess) {
-            // no room for them: the mesh keeps two launches per step
-            (void)hipGetLastError();
-            c->d_tiles = nullptr;
-            return SWE_OK;
+        if (nt > held) {
+            // with room for the next shorter lengths, which most meshes end at
+            // (an allocation and a free take as long as a try)
+            const int last = std::max(least, len - 24);
+            free_tiles(c);
+            held = (size_t)((c->ne + last - 1) / last);
+            if (dev_alloc(&c->d_tiles, held * TILE_BYTES) != hipSuccess) {
+                // no room for them: the mesh keeps two launches per step
+                (void)hipGetLastError();
+                c->d_tiles = nullptr;
+                return SWE_OK;
+            }
         }
         TileView t{};
         t.items = static_cast<unsigned *>(c->d_tiles);
@@ -1206,9 +1214,9 @@ swe_status build_tiles(swe_ctx *c)
             c->tiles = t;
             return SWE_OK;
         }
-        free_tiles(c);
         len -= std::max(8, over[0] / 8 * 8);
     }
+    free_tiles(c);
     return SWE_OK;
 }
 
