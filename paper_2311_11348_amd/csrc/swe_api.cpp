@@ -1479,6 +1479,17 @@ int64_t pool_bytes(int p, bool fp32, int64_t nc)
 
 }  // namespace
 
+// What an entry returns when host memory runs out in it (nothing else throws;
+// the text is short enough to be kept without an allocation).
+template <typename T>
+swe_status no_host_memory(T *c)
+{
+    if (c) c->err = "no host memory";
+    return SWE_ENOMEM;
+}
+
+#define SWE_CATCH(c) catch (...) { return no_host_memory(c); }
+
 extern "C" {
 
 void swe_config_default(swe_config *cfg)
@@ -1495,7 +1506,7 @@ void swe_config_default(swe_config *cfg)
 }
 
 swe_status swe_create(const swe_config *cfg, swe_ctx **out)
-{
+try {
     if (!cfg || !out) return SWE_EINVAL;
     *out = nullptr;
     if (cfg->precision != SWE_FP64 && cfg->precision != SWE_FP32_WB) return SWE_EINVAL;
@@ -1556,7 +1567,7 @@ swe_status swe_create(const swe_config *cfg, swe_ctx **out)
     ring_hold();
     *out = c;
     return SWE_OK;
-}
+} SWE_CATCH(static_cast<swe_ctx *>(nullptr))
 
 void swe_destroy(swe_ctx *c)
 {
@@ -1594,7 +1605,7 @@ int64_t swe_footprint_bytes(int64_t ne, int p_max, int precision)
 
 swe_status swe_set_mesh(swe_ctx *c, int64_t nv, const double *vxy, int64_t ne, const int32_t *tri,
                         const int8_t *tag)
-{
+try {
     if (!c) return SWE_EINVAL;
     if (c->batch) return fail(c, SWE_EINVAL, "context is resident in a batch");
     if (nv < 3 || ne < 1 || !vxy || !tri) return fail(c, SWE_EINVAL, "empty mesh");
@@ -1759,10 +1770,10 @@ swe_status swe_set_mesh(swe_ctx *c, int64_t nv, const double *vxy, int64_t ne, c
     c->failed = false;
     c->have_mesh = true;
     return SWE_OK;
-}
+} SWE_CATCH(c)
 
 swe_status swe_set_bathymetry(swe_ctx *c, const double *hb)
-{
+try {
     if (!c || !hb) return SWE_EINVAL;
     if (c->batch) return fail(c, SWE_EINVAL, "context is resident in a batch");
     if (!c->have_mesh) return fail(c, SWE_EINVAL, "set_mesh first");
@@ -1778,10 +1789,10 @@ swe_status swe_set_bathymetry(swe_ctx *c, const double *hb)
     HIP_TRY(c, usolve_buf(c, 0));
     HIP_TRY(c, hipStreamSynchronize(c->s_base));
     return SWE_OK;
-}
+} SWE_CATCH(c)
 
 swe_status swe_set_order(swe_ctx *c, const int8_t *p)
-{
+try {
     if (!c || !p) return SWE_EINVAL;
     if (c->batch) return fail(c, SWE_EINVAL, "context is resident in a batch");
     if (!c->have_mesh) return fail(c, SWE_EINVAL, "set_mesh first");
@@ -1803,20 +1814,20 @@ swe_status swe_set_order(swe_ctx *c, const int8_t *p)
     st = build_lists(c);
     if (st) return st;
     return swe_set_state(c, t, coef.data());
-}
+} SWE_CATCH(c)
 
 swe_status swe_get_order(swe_ctx *c, int8_t *p)
-{
+try {
     if (!c || !p) return SWE_EINVAL;
     if (!c->have_mesh) return fail(c, SWE_EINVAL, "set_mesh first");
     if (swe_status st = refresh_orders(c)) return st;   // orders change on the device every step
     for (int64_t i = 0; i < c->ne; ++i) p[c->e_perm[i]] = c->p[i];
     return SWE_OK;
-}
+} SWE_CATCH(c)
 
 swe_status swe_set_open_boundary(swe_ctx *c, int ncon, const double *amp, const double *omega,
                                  const double *phase)
-{
+try {
     if (!c || ncon < 0 || ncon > NCON_MAX) return SWE_EINVAL;
     if (ncon > 0 && (!amp || !omega || !phase)) return SWE_EINVAL;
     c->ncon = ncon;
@@ -1826,10 +1837,10 @@ swe_status swe_set_open_boundary(swe_ctx *c, int ncon, const double *amp, const 
         c->phase[i] = phase[i];
     }
     return SWE_OK;
-}
+} SWE_CATCH(c)
 
 swe_status swe_set_state(swe_ctx *c, double t0, const double *coef)
-{
+try {
     if (!c || !coef) return SWE_EINVAL;
     if (c->batch) return fail(c, SWE_EINVAL, "context is resident in a batch");
     if (!c->have_mesh) return fail(c, SWE_EINVAL, "set_mesh first");
@@ -1848,10 +1859,10 @@ swe_status swe_set_state(swe_ctx *c, double t0, const double *coef)
     c->t = t0;
     c->failed = false;
     return SWE_OK;
-}
+} SWE_CATCH(c)
 
 swe_status swe_project_points(swe_ctx *c, double *xy)
-{
+try {
     if (!c || !xy) return SWE_EINVAL;
     if (!c->have_mesh) return fail(c, SWE_EINVAL, "set_mesh first");
     const int S = c->stride;
@@ -1864,10 +1875,10 @@ swe_status swe_project_points(swe_ctx *c, double *xy)
         }
     }
     return SWE_OK;
-}
+} SWE_CATCH(c)
 
 swe_status swe_set_state_points(swe_ctx *c, double t0, const double *vals)
-{
+try {
     if (!c || !vals) return SWE_EINVAL;
     if (!c->have_mesh) return fail(c, SWE_EINVAL, "set_mesh first");
     if (swe_status st = refresh_orders(c)) return st;
@@ -1886,10 +1897,10 @@ swe_status swe_set_state_points(swe_ctx *c, double t0, const double *vals)
             }
     }
     return swe_set_state(c, t0, coef.data());
-}
+} SWE_CATCH(c)
 
 swe_status swe_set_source(swe_ctx *c, const double *coef)
-{
+try {
     if (!c) return SWE_EINVAL;
     if (c->batch) return fail(c, SWE_EINVAL, "context is resident in a batch");
     if (!c->have_mesh) return fail(c, SWE_EINVAL, "set_mesh first");
@@ -1909,7 +1920,7 @@ swe_status swe_set_source(swe_ctx *c, const double *coef)
     HIP_TRY(c, dzero(c, c->d_C[1], bytes));
     HIP_TRY(c, hipStreamSynchronize(c->s_base));
     return SWE_OK;
-}
+} SWE_CATCH(c)
 
 swe_status swe_step_form(const swe_ctx *c, int *form, int *tile, int *flux_groups)
 {
@@ -1933,7 +1944,7 @@ swe_status swe_step_form(const swe_ctx *c, int *form, int *tile, int *flux_group
 }
 
 swe_status swe_step(swe_ctx *c, int64_t nsteps, double dt)
-{
+try {
     if (!c) return SWE_EINVAL;
     if (c->batch) return fail(c, SWE_EINVAL, "context is resident in a batch");
     if (!c->have_mesh) return fail(c, SWE_EINVAL, "set_mesh first");
@@ -1983,10 +1994,10 @@ swe_status swe_step(swe_ctx *c, int64_t nsteps, double dt)
         c->t = t0 + (double)(s + 1) * dt;
     }
     return SWE_OK;
-}
+} SWE_CATCH(c)
 
 swe_status swe_sync(swe_ctx *c)
-{
+try {
     if (!c) return SWE_EINVAL;
     HIP_TRY(c, hipStreamSynchronize(c->s_base));
     HIP_TRY(c, hipStreamSynchronize(c->s_corr));
@@ -1999,14 +2010,14 @@ swe_status swe_sync(swe_ctx *c)
         }
     }
     return SWE_OK;
-}
+} SWE_CATCH(c)
 
 swe_status swe_batch_sync(swe_batch *b);
 double batch_member_time(swe_batch *b, int slot);
 swe_status batch_member_state(swe_batch *b, int slot, double *coef, double *t_out);
 
 swe_status swe_get_state(swe_ctx *c, double *coef, double *t_out)
-{
+try {
     if (!c || !coef) return SWE_EINVAL;
     if (!c->have_mesh) return fail(c, SWE_EINVAL, "set_mesh first");
     if (c->batch) {
@@ -2021,10 +2032,10 @@ swe_status swe_get_state(swe_ctx *c, double *coef, double *t_out)
     swe_status st = download(c, c->d_C[0], 3, coef);
     if (t_out) *t_out = c->t;
     return st;
-}
+} SWE_CATCH(c)
 
 swe_status swe_mass(swe_ctx *c, double *out)
-{
+try {
     if (!c || !out) return SWE_EINVAL;
     if (!c->have_mesh) return fail(c, SWE_EINVAL, "set_mesh first");
     if (c->batch) {
@@ -2038,7 +2049,7 @@ swe_status swe_mass(swe_ctx *c, double *out)
     HIP_TRY(c, hipStreamSynchronize(c->s_base));
     if (c->batch) release_state_buffers(c);
     return SWE_OK;
-}
+} SWE_CATCH(c)
 
 swe_status swe_mass_noalloc(swe_ctx *c, double *d_out)
 {
@@ -2053,7 +2064,7 @@ swe_status swe_mass_noalloc(swe_ctx *c, double *d_out)
 }
 
 swe_status swe_rhs(swe_ctx *c, double t, const double *coef, double *rhs)
-{
+try {
     if (!c || !coef || !rhs) return SWE_EINVAL;
     if (c->batch) return fail(c, SWE_EINVAL, "context is resident in a batch");
     if (!c->have_mesh) return fail(c, SWE_EINVAL, "set_mesh first");
@@ -2066,10 +2077,10 @@ swe_status swe_rhs(swe_ctx *c, double t, const double *coef, double *rhs)
     if (e != hipSuccess) return fail(c, SWE_EDEVICE, std::string("rhs launch: ") + hipGetErrorString(e));
     HIP_TRY(c, hipStreamSynchronize(c->s_base));
     return download_scratch(c, c->d_L, rhs);
-}
+} SWE_CATCH(c)
 
 swe_status swe_usolve(swe_ctx *c, const double *coef, double *u_out)
-{
+try {
     if (!c || !coef || !u_out) return SWE_EINVAL;
     if (c->batch) return fail(c, SWE_EINVAL, "context is resident in a batch");
     if (!c->have_mesh) return fail(c, SWE_EINVAL, "set_mesh first");
@@ -2079,10 +2090,10 @@ swe_status swe_usolve(swe_ctx *c, const double *coef, double *u_out)
     HIP_TRY(c, usolve_buf(c, 1));
     HIP_TRY(c, hipStreamSynchronize(c->s_base));
     return download(c, c->d_U[1], 2, u_out);
-}
+} SWE_CATCH(c)
 
 swe_status swe_rhs_split(swe_ctx *c, double t, const double *coef, double *base_out, double *corr_out)
-{
+try {
     if (!c || !coef || !base_out || !corr_out) return SWE_EINVAL;
     if (!c->have_mesh) return fail(c, SWE_EINVAL, "set_mesh first");
     if (!separated(c)) return fail(c, SWE_EINVAL, "context is not order-separated (separate = 1, p_base < p_max)");
@@ -2099,10 +2110,10 @@ swe_status swe_rhs_split(swe_ctx *c, double t, const double *coef, double *base_
     st = download_scratch(c, c->d_L, base_out);
     if (st) return st;
     return download(c, c->d_Lc, 3, corr_out);
-}
+} SWE_CATCH(c)
 
 swe_status swe_indicator(swe_ctx *c, double t, const double *coef, double *I_out)
-{
+try {
     if (!c || !coef || !I_out) return SWE_EINVAL;
     if (!c->have_mesh) return fail(c, SWE_EINVAL, "set_mesh first");
     if (!c->d_I) return fail(c, SWE_EINVAL, "indicator needs a context with adapt = 1");
@@ -2128,7 +2139,7 @@ swe_status swe_indicator(swe_ctx *c, double t, const double *coef, double *I_out
     HIP_TRY(c, d2h(c, h.data(), c->d_I, sizeof(double) * c->ne));
     for (int64_t i = 0; i < c->ne; ++i) I_out[c->e_perm[i]] = h[i];
     return SWE_OK;
-}
+} SWE_CATCH(c)
 
 
 // ----------------------------------------------------------------------------
@@ -2601,7 +2612,7 @@ swe_status batch_member_state(swe_batch *b, int slot, double *coef, double *t_ou
 extern "C" {
 
 swe_status swe_batch_create(const swe_config *cfg, int64_t budget, int max_instances, swe_batch **out)
-{
+try {
     if (!cfg || !out || budget <= 0 || max_instances <= 0 || max_instances > 65536) return SWE_EINVAL;
     if (cfg->precision != SWE_FP64 && cfg->precision != SWE_FP32_WB) return SWE_EINVAL;
     *out = nullptr;
@@ -2645,7 +2656,7 @@ swe_status swe_batch_create(const swe_config *cfg, int64_t budget, int max_insta
     }
     *out = b;
     return SWE_OK;
-}
+} SWE_CATCH(static_cast<swe_ctx *>(nullptr))
 
 void swe_batch_destroy(swe_batch *b)
 {
@@ -2659,19 +2670,22 @@ void swe_batch_destroy(swe_batch *b)
             c->t = b->h_inst[i].t;
             c->batch = nullptr;
             c->slot = -1;
-            if (restore_neighbours(c) == SWE_OK) (void)build_items(c);
+            try {
+                if (restore_neighbours(c) == SWE_OK) (void)build_items(c);
+            } catch (...) {
+                // without edge items it steps on the gather kernel
+            }
         }
     drop_graph(b);
-    std::vector<void *> ptrs = {b->d_inst, b->d_flags, b->d_ntiles, b->d_natiles, b->d_vtx};
+    for (void *q : {(void *)b->d_inst, (void *)b->d_flags, (void *)b->d_ntiles, (void *)b->d_natiles, (void *)b->d_vtx})
+        if (q) (void)dev_free(q);
     for (int p = 0; p < 4; ++p) {
         const PoolView &v = b->pool[p].v;
         for (void *q : {v.C0, v.C1, v.U0, v.U1, (void *)v.ev, (void *)v.nb, (void *)v.nbk, (void *)v.ep,
                         (void *)v.pnew, (void *)v.items, (void *)v.nitems, (void *)b->d_tiles[p],
                         (void *)b->d_atiles[p]})
-            ptrs.push_back(q);
+            if (q) (void)dev_free(q);
     }
-    for (void *q : ptrs)
-        if (q) (void)dev_free(q);
     if (b->fork) (void)hipEventDestroy(b->fork);
     for (int i = 0; i < 3; ++i) {
         if (b->join[i]) (void)hipEventDestroy(b->join[i]);
@@ -2693,7 +2707,7 @@ int swe_batch_resident(const swe_batch *b)
 }
 
 swe_status swe_batch_admit(swe_batch *b, swe_ctx *c, int64_t nsteps, double dt, int32_t *slot)
-{
+try {
     if (!b || !c || !slot || nsteps < 0 || !(dt > 0.0)) return SWE_EINVAL;
     if (!c->have_mesh) return bfail(b, SWE_EINVAL, "context has no mesh");
     if (c->batch) return bfail(b, SWE_EINVAL, "context is already resident in a batch");
@@ -2807,10 +2821,10 @@ swe_status swe_batch_admit(swe_batch *b, swe_ctx *c, int64_t nsteps, double dt, 
     if (st) return st;
     *slot = i;
     return SWE_OK;
-}
+} SWE_CATCH(b)
 
 swe_status swe_batch_tick(swe_batch *b, int64_t nsteps)
-{
+try {
     if (!b || nsteps < 0) return SWE_EINVAL;
     if (nsteps == 0 || swe_batch_resident(b) == 0) return SWE_OK;
     if (b->graph_orders < 0) {
@@ -2846,17 +2860,17 @@ swe_status swe_batch_tick(swe_batch *b, int64_t nsteps)
                 if (e == hipSuccess) e = j;
             }
     return e == hipSuccess ? SWE_OK : bfail(b, SWE_EDEVICE, std::string("step graph launch: ") + hipGetErrorString(e));
-}
+} SWE_CATCH(b)
 
 swe_status swe_batch_sync(swe_batch *b)
-{
+try {
     if (!b) return SWE_EINVAL;
     BHIP_TRY(b, hipStreamSynchronize(b->s));
     return SWE_OK;
-}
+} SWE_CATCH(b)
 
 swe_status swe_batch_query(swe_batch *b, int32_t slot, int64_t *steps_left, double *t, int *failed)
-{
+try {
     if (!b || slot < 0 || slot >= b->cap || !b->mem[slot].ctx) return SWE_EINVAL;
     swe_status st = get_desc(b, slot);
     if (st) return st;
@@ -2867,10 +2881,10 @@ swe_status swe_batch_query(swe_batch *b, int32_t slot, int64_t *steps_left, doub
     if (t) *t = b->h_inst[slot].t;
     if (failed) *failed = f;
     return SWE_OK;
-}
+} SWE_CATCH(b)
 
 swe_status swe_batch_poll(swe_batch *b, int32_t *slots, int32_t *failed, int max, int *n)
-{
+try {
     if (!b || !slots || !failed || !n || max < 0) return SWE_EINVAL;
     std::vector<int> flags(b->cap);
     BHIP_TRY(b, hipMemcpyAsync(b->h_inst.data(), b->d_inst, sizeof(InstDesc) * b->cap, hipMemcpyDeviceToHost, b->s));
@@ -2887,10 +2901,10 @@ swe_status swe_batch_poll(swe_batch *b, int32_t *slots, int32_t *failed, int max
     }
     *n = k;
     return SWE_OK;
-}
+} SWE_CATCH(b)
 
 swe_status swe_batch_retire(swe_batch *b, int32_t slot)
-{
+try {
     if (!b || slot < 0 || slot >= b->cap || !b->mem[slot].ctx) return SWE_EINVAL;
     swe_batch::Member &m = b->mem[slot];
     swe_ctx *c = m.ctx;
@@ -2929,7 +2943,7 @@ swe_status swe_batch_retire(swe_batch *b, int32_t slot)
     if (!any_order) release_pool(b, order);
     if (!any) release_vertices(b);
     return upload_tiles(b);
-}
+} SWE_CATCH(b)
 
 swe_status swe_batch_tile_config(const swe_batch *b, int p, int *tile, int *grid, int *shared)
 {
@@ -2941,7 +2955,7 @@ swe_status swe_batch_tile_config(const swe_batch *b, int p, int *tile, int *grid
 }
 
 swe_status swe_batch_set_tile(swe_batch *b, int p, int tile, int shared)
-{
+try {
     if (!b || p < 0 || p > 3) return SWE_EINVAL;
     if (shared) {
         if (tile != BLOCK) return bfail(b, SWE_EINVAL, "the shared-flux kernel takes 256-element tiles");
@@ -2956,10 +2970,10 @@ swe_status swe_batch_set_tile(swe_batch *b, int p, int tile, int shared)
     b->grid[p] = 0;
     drop_graph(b);
     return upload_tiles(b);
-}
+} SWE_CATCH(b)
 
 swe_status swe_batch_tune(swe_batch *b, int reps)
-{
+try {
     if (!b || reps <= 0) return SWE_EINVAL;
     BHIP_TRY(b, hipStreamSynchronize(b->s));
     // every resident instance takes part without advancing: stage 1 reads
@@ -3037,6 +3051,6 @@ swe_status swe_batch_tune(swe_batch *b, int reps)
     if (st == SWE_OK) st = upload_tiles(b);
     drop_graph(b);
     return st;
-}
+} SWE_CATCH(b)
 
 }  // extern "C"

@@ -164,3 +164,59 @@ def test_reading_and_stepping_leave_captures_elsewhere_alone(lib):
             assert count("tile builds") == 1 and count("pinned allocations") == 1
             assert count("allocations a capture elsewhere forbids") == before
     """)
+
+
+def test_no_entry_throws_when_host_memory_runs_out(lib):
+    """Every call that takes host memory is refused with SWE_ENOMEM (or goes on
+    without it); with memory again the same objects work."""
+    host_runtime.run(lib, """
+        def refused(call):
+            L.fake_refuse_new(1)
+            st = call()
+            L.fake_refuse_new(0)
+            assert st in (swe.SWE_OK, swe.SWE_ENOMEM), st
+            return st == swe.SWE_ENOMEM
+
+        prob = I.config_dambreak(n=12)
+        m = prob.mesh
+        p32, p8 = ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int8)
+        vxy, tri, tag = (np.ascontiguousarray(a) for a in (m.vxy, m.tri.astype(np.int32), m.tag.astype(np.int8)))
+        order = np.ascontiguousarray(prob.p)
+        names = []
+        with swe.context_for(prob, separate=2) as ctx, swe.context_for(I.config_c2(n=9, p=2)) as member:
+            c, hb = np.zeros((ctx.ne, 3, ctx.K)), np.ascontiguousarray(prob.hb_vertex)
+            pts, t = np.zeros((ctx.ne, swe.SWE_NQP, 3)), ctypes.c_double()
+            d = swe._d
+            calls = {
+                "mesh": lambda: L.swe_set_mesh(ctx.h, len(vxy), d(vxy), ctx.ne, tri.ctypes.data_as(p32), tag.ctypes.data_as(p8)),
+                "bathymetry": lambda: L.swe_set_bathymetry(ctx.h, d(hb)),
+                "order": lambda: L.swe_set_order(ctx.h, order.ctypes.data_as(p8)),
+                "points": lambda: L.swe_set_state_points(ctx.h, 0.0, d(pts)),
+                "state": lambda: L.swe_set_state(ctx.h, 0.0, d(c)),
+                "source": lambda: L.swe_set_source(ctx.h, d(c)),
+                "step": lambda: L.swe_step(ctx.h, 9, 1e-5),
+                "sync": lambda: L.swe_sync(ctx.h),
+                "get": lambda: L.swe_get_state(ctx.h, d(c), ctypes.byref(t)),
+                "rhs": lambda: L.swe_rhs(ctx.h, 0.0, d(c), d(c.copy())),
+            }
+            for name, call in calls.items():
+                if refused(call):
+                    names.append(name)
+                    assert b"no host memory" in L.swe_last_error(ctx.h)
+                assert call() == swe.SWE_OK, name
+            slot, n = ctypes.c_int32(), ctypes.c_int()
+            with swe.Batch(budget_bytes=64 << 20, max_instances=4) as b:
+                refused(lambda: L.swe_batch_admit(b.h, member.h, 9, 1.0, ctypes.byref(slot)))
+                if L.swe_batch_resident(b.h) == 0:
+                    assert L.swe_batch_admit(b.h, member.h, 9, 1.0, ctypes.byref(slot)) == swe.SWE_OK
+                refused(lambda: L.swe_batch_tick(b.h, 9))
+                slots = (ctypes.c_int32 * 4)()
+                refused(lambda: L.swe_batch_poll(b.h, slots, (ctypes.c_int32 * 4)(), 4, ctypes.byref(n)))
+                refused(lambda: L.swe_batch_tune(b.h, 1))
+                L.fake_refuse_new(1)
+                L.swe_batch_destroy(b.h)
+                L.fake_refuse_new(0)
+                b.h = None
+            member.step(2, 1.0)
+        assert {"mesh", "order", "points", "step"} <= set(names), names
+    """)
